@@ -17,6 +17,11 @@ extern "C" {
  * frag layout (vla_debug_pack_frag).  Requires K % 32 == 0, N % 64 == 0. */
 int vla_debug_gemm(const void* A, const void* W, int32_t M, int32_t N, int32_t K, float* C, void* stream);
 
+/* vla_debug_gemm on one of the GEMM's tile shapes, 0 .. 8 (0: 256 x 256, the others smaller; -1: the shape the
+ * library picks for these sizes, as vla_debug_gemm).  Every shape gives the same bits. */
+int vla_debug_gemm_shape(const void* A, const void* W, int32_t M, int32_t N, int32_t K, int32_t shape, float* C,
+                         void* stream);
+
 /* Decode skinny GEMM: C[M, N] fp32 = A * W^T for M <= 128, A [M, K] and W
  * [N, K] in frag layout, on a persistent grid of at most `workgroups`
  * workgroups; tile segments' partial sums go to `scratch` (16 * M * N floats).

@@ -43,8 +43,9 @@ int scratch_on_current_device(float** out) {
 
 extern "C" {
 
-int vla_debug_gemm(const void* A, const void* W, int32_t M, int32_t N, int32_t K, float* C, void* stream) {
-  if (!A || !W || !C || M < 0 || N < 0 || K <= 0) return VLA_EINVAL;
+int vla_debug_gemm_shape(const void* A, const void* W, int32_t M, int32_t N, int32_t K, int32_t shape, float* C,
+                         void* stream) {
+  if (!A || !W || !C || M < 0 || N < 0 || K <= 0 || shape < -1 || shape >= kGemmShapes) return VLA_EINVAL;
   GemmArgs g{};
   g.A = static_cast<const bf16_t*>(A);
   g.W = static_cast<const bf16_t*>(W);
@@ -53,7 +54,11 @@ int vla_debug_gemm(const void* A, const void* W, int32_t M, int32_t N, int32_t K
   g.K = K;
   g.C = C;
   g.ldc = N;
-  return launch_gemm(g, kEpiStoreF32, static_cast<hipStream_t>(stream)) == hipSuccess ? VLA_OK : VLA_EHIP;
+  return launch_gemm(g, kEpiStoreF32, static_cast<hipStream_t>(stream), shape) == hipSuccess ? VLA_OK : VLA_EHIP;
+}
+
+int vla_debug_gemm(const void* A, const void* W, int32_t M, int32_t N, int32_t K, float* C, void* stream) {
+  return vla_debug_gemm_shape(A, W, M, N, K, -1, C, stream);
 }
 
 int vla_debug_skinny(const void* A, const void* W, int32_t M, int32_t N, int32_t K, int32_t workgroups,

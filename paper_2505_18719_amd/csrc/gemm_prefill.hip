@@ -444,13 +444,17 @@ static int persistent_workgroups() {
   return cus[dev];
 }
 
-hipError_t launch_gemm(const GemmArgs& a, GemmEpilogue epi, hipStream_t s) {
+hipError_t launch_gemm(const GemmArgs& a, GemmEpilogue epi, hipStream_t s, int shape) {
   if (a.M <= 0 || a.N <= 0) return hipSuccess;
   // frag-layout operands, 32-bit byte offsets into them
   const int ka = a.ka ? a.ka : a.K, kw = a.kw ? a.kw : a.K;
   if (a.K % BK != 0 || a.N % 64 != 0 || ka < a.K || kw < a.K || ka % 32 != 0 || kw % 32 != 0 ||
       (long long)frag_elems(a.M, ka) * 2 >= (1ll << 31) || (long long)frag_elems(a.N, kw) * 2 >= (1ll << 31))
     return hipErrorInvalidValue;
+  if (epi == kEpiSwiGluKeep && (!a.C || a.ldc % 4 != 0 || a.ldc < a.N)) return hipErrorInvalidValue;
+  if (shape >= kGemmShapes) return hipErrorInvalidValue;
+  if (shape < 0) shape = gemm_shape(a.M, a.N, a.K, persistent_workgroups());
+  if (shape > 0) return launch_gemm_shape(a, epi, shape, s);
   const int tm = (a.M + BM - 1) / BM, tn = (a.N + BN - 1) / BN;
   const dim3 grid(std::min(tm * tn, persistent_workgroups())), block(NT);
   switch (epi) {
@@ -459,7 +463,6 @@ hipError_t launch_gemm(const GemmArgs& a, GemmEpilogue epi, hipStream_t s) {
     case kEpiSwiGlu: hipLaunchKernelGGL(gemm_bf16_kernel<kEpiSwiGlu>, grid, block, 0, s, a, tm, tn); break;
     case kEpiQkvRope: hipLaunchKernelGGL(gemm_bf16_kernel<kEpiQkvRope>, grid, block, 0, s, a, tm, tn); break;
     case kEpiSwiGluKeep:
-      if (!a.C || a.ldc % 4 != 0 || a.ldc < a.N) return hipErrorInvalidValue;
       hipLaunchKernelGGL(gemm_bf16_kernel<kEpiSwiGluKeep>, grid, block, 0, s, a, tm, tn);
       break;
   }

@@ -58,7 +58,12 @@ struct GemmArgs {
   int d_model, n_heads, head_dim;
 };
 
-hipError_t launch_gemm(const GemmArgs& a, GemmEpilogue epi, hipStream_t s);
+// Tile shapes of the prefill GEMM: 0 the 256 x 256 kernel of gemm_prefill.hip, the others gemm_tiles.hip's.  The
+// results are the same bits from each; launch_gemm runs gemm_shape's choice unless given a shape (test hook).
+hipError_t launch_gemm(const GemmArgs& a, GemmEpilogue epi, hipStream_t s, int shape = -1);
+constexpr int kGemmShapes = 9;
+int gemm_shape(int M, int N, int K, int cus);
+hipError_t launch_gemm_shape(const GemmArgs& a, GemmEpilogue epi, int shape, hipStream_t s);
 
 // Skinny GEMM for decode: C = A[M, K] * W[N, K]^T for M <= 128 rows, N % 64 == 0,
 // K % 256 == 0, N * K < 2^30.  The work is cut into units of 64 columns

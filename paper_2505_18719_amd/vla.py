@@ -31,7 +31,7 @@ PROJECTIONS = ("wq", "wk", "wv", "wo", "wgate", "wup", "wdown")
 PROF_CATEGORIES = ("prefill_gemm", "prefill_attn", "decode_gemm", "decode_attn", "decode_layer")
 # training modes of vla_ppo_lora_grads (VLA_TRAIN_*): recompute each layer's forward, or keep it
 TRAIN_RECOMPUTE, TRAIN_KEEP = 0, 1
-DEBUG_EXPORTS = ("vla_debug_gemm", "vla_debug_skinny", "vla_debug_pack_frag", "vla_debug_sample", "vla_debug_read",
+DEBUG_EXPORTS = ("vla_debug_gemm", "vla_debug_gemm_shape", "vla_debug_skinny", "vla_debug_pack_frag", "vla_debug_sample", "vla_debug_read",
                  "vla_debug_set_layer_limit", "vla_debug_set_stop", "vla_debug_skinny_noalloc",
                  "vla_debug_set_decode_path", "vla_debug_trace_decode_layer")
 
@@ -97,6 +97,7 @@ def load_library(path: str = LIB_PATH) -> ctypes.CDLL:
     lib.vla_destroy.restype = None
     lib.vla_last_error.restype = ctypes.c_char_p
     lib.vla_debug_gemm.argtypes = [vp, vp, i32, i32, i32, vp, vp]
+    lib.vla_debug_gemm_shape.argtypes = [vp, vp, i32, i32, i32, i32, vp, vp]
     lib.vla_debug_skinny.argtypes = [vp, vp, i32, i32, i32, i32, vp, vp, vp]
     lib.vla_debug_skinny_noalloc.argtypes = [vp, vp, i32, i32, i32, i32, vp, vp]
     lib.vla_debug_pack_frag.argtypes = [vp, i32, i32, i32, vp, vp]
@@ -367,13 +368,13 @@ def debug_pack_frag(X: torch.Tensor) -> torch.Tensor:
     return out
 
 
-def debug_gemm(A: torch.Tensor, W: torch.Tensor) -> torch.Tensor:
+def debug_gemm(A: torch.Tensor, W: torch.Tensor, shape: int = -1) -> torch.Tensor:
     lib = load_library()
     M, K = A.shape
     N = W.shape[0]
     Af, Wf = debug_pack_frag(A), debug_pack_frag(W)
     C = torch.empty(M, N, dtype=torch.float32, device=A.device)
-    _check(lib.vla_debug_gemm(_ptr(Af), _ptr(Wf), M, N, K, _ptr(C), _stream(A.device)))
+    _check(lib.vla_debug_gemm_shape(_ptr(Af), _ptr(Wf), M, N, K, shape, _ptr(C), _stream(A.device)))
     return C
 
 

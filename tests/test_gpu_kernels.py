@@ -107,3 +107,18 @@ def test_sampler_matches_oracle(T):
     assert torch.equal(out["logits"][:, 2].cpu(), torch.from_numpy(z))
     assert torch.equal(out["next"].cpu(), out["tokens"][:, 2].cpu())
     assert bool((out["tokens"][:, [0, 1, 3, 4, 5, 6]] == -1).all())   # other steps untouched
+
+
+# one row, rows and columns on and beside the edges of every shape's tile (64 ... 160 rows, 64 ... 192 columns), K of an
+# even and an odd number of 32-wide steps, down to one and fewer than any ring holds
+@pytest.mark.parametrize("M,N,K", [(1, 64, 32), (63, 128, 96), (64, 192, 64), (97, 320, 704), (160, 384, 288),
+                                   (161, 448, 1024), (277, 1088, 224), (640, 768, 1376)])
+def test_prefill_gemm_shapes_give_the_same_bits(M, N, K):
+    from paper_2505_18719_amd import vla
+    A, W = _rand_bf16((M, K), 21), _rand_bf16((N, K), 22, 0.02)
+    ref = vla.debug_gemm(A, W, shape=0)
+    _check_matmul(ref, A, W, "gemm-256")
+    for shape in range(1, 9):
+        C = vla.debug_gemm(A, W, shape=shape)
+        torch.cuda.synchronize()
+        assert torch.equal(C, ref), shape
