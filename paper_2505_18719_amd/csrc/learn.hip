@@ -4,6 +4,8 @@
 // gradient of those log-probabilities w.r.t. the action logits.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "common.h"
 #include "kernels.h"
 
@@ -11,6 +13,35 @@ namespace vla {
 namespace {
 
 constexpr int kGaeChunks = 16;  // waves per workgroup; each takes one slice of the time axis
+
+// Steps t1 - 1 .. t0 of environment n, last first: step(t, delta_t, gamma lam (1 - d_{t+1}), V_t).  The recursion is
+// serial but its inputs are not, so kGaeAhead steps' loads go out together (a window has few waves to cover a load's
+// latency: 256 environments are 4 workgroups, 15.0 -> 10.2 us at 256 x 256).
+constexpr int kGaeAhead = 8;
+template <class F>
+__device__ __forceinline__ void gae_steps(const GaeArgs& a, int n, int t0, int t1, F step) {
+  const size_t N = a.n_env;
+  const float gl = a.gamma * a.lam;
+  float vn = a.values[t1 * N + n];
+  for (int t = t1 - 1; t >= t0; t -= kGaeAhead) {
+    float r[kGaeAhead], v[kGaeAhead];
+    uint8_t d[kGaeAhead];
+#pragma unroll
+    for (int u = 0; u < kGaeAhead; ++u)
+      if (t - u >= t0) {
+        r[u] = a.rewards[(t - u) * N + n];
+        v[u] = a.values[(t - u) * N + n];
+        d[u] = a.dones[(t - u + 1) * N + n];
+      }
+#pragma unroll
+    for (int u = 0; u < kGaeAhead; ++u)
+      if (t - u >= t0) {
+        const float c = d[u] ? 0.f : 1.f;
+        step(t - u, r[u] + a.gamma * c * vn - v[u], gl * c, v[u]);
+        vn = v[u];
+      }
+  }
+}
 
 // One workgroup per 64 environments, wave w the time slice [t0_w, t1_w).
 // The recursion A_t = delta_t + k_t A_{t+1} (k_t = gamma lam (1 - d_{t+1}))
@@ -27,18 +58,12 @@ __global__ __launch_bounds__(64 * kGaeChunks) void gae_kernel(GaeArgs a) {
   const int L = (M + kGaeChunks - 1) / kGaeChunks;
   const int t0 = min(M, w * L), t1 = min(M, t0 + L);
   const bool live = n < N;
-  const float gl = a.gamma * a.lam;
   float p = 0.f, q = 1.f;
   if (live) {
-    float vn = a.values[(size_t)t1 * N + n];
-    for (int t = t1 - 1; t >= t0; --t) {
-      const float c = a.dones[(size_t)(t + 1) * N + n] ? 0.f : 1.f;
-      const float v = a.values[(size_t)t * N + n];
-      const float delta = a.rewards[(size_t)t * N + n] + a.gamma * c * vn - v;
-      p = delta + gl * c * p;
-      q = gl * c * q;
-      vn = v;
-    }
+    gae_steps(a, n, t0, t1, [&](int, float delta, float kc, float) {
+      p = delta + kc * p;
+      q = kc * q;
+    });
   }
   P[w][lane] = p;
   Q[w][lane] = q;
@@ -53,15 +78,57 @@ __global__ __launch_bounds__(64 * kGaeChunks) void gae_kernel(GaeArgs a) {
   __syncthreads();
   if (!live) return;
   float adv = Ain[w][lane];
-  float vn = a.values[(size_t)t1 * N + n];
-  for (int t = t1 - 1; t >= t0; --t) {
-    const float c = a.dones[(size_t)(t + 1) * N + n] ? 0.f : 1.f;
-    const float v = a.values[(size_t)t * N + n];
-    const float delta = a.rewards[(size_t)t * N + n] + a.gamma * c * vn - v;
-    adv = delta + gl * c * adv;
+  gae_steps(a, n, t0, t1, [&](int t, float delta, float kc, float v) {
+    adv = delta + kc * adv;
     a.advantages[(size_t)t * N + n] = adv;
     if (a.returns) a.returns[(size_t)t * N + n] = adv + v;
-    vn = v;
+  });
+}
+
+// The surrogate of action t: its term and clip flag are added to (surr, clip), its token gradient is returned.  The
+// token loads are unrolled to the largest n_tokens, so that they are in flight together.
+constexpr int kPpoMaxTokens = 16;
+__device__ __forceinline__ float ppo_action(const PpoArgs& a, int t, float& surr, float& clip) {
+  const float* ln = a.logp_new + (size_t)t * a.n_tokens;
+  const float* lo = a.logp_old + (size_t)t * a.n_tokens;
+  float vn[kPpoMaxTokens], vo[kPpoMaxTokens];
+  const float A = a.advantages[t];
+#pragma unroll
+  for (int i = 0; i < kPpoMaxTokens; ++i)
+    if (i < a.n_tokens) {
+      vn[i] = ln[i];
+      vo[i] = lo[i];
+    }
+  float sn = 0.f, so = 0.f;
+#pragma unroll
+  for (int i = 0; i < kPpoMaxTokens; ++i)
+    if (i < a.n_tokens) {
+      sn += vn[i];
+      so += vo[i];
+    }
+  const float rho = expf(sn - so);
+  const float rc = fminf(fmaxf(rho, 1.f - a.eps), 1.f + a.eps);
+  const bool clipped = (A > 0.f && rho > 1.f + a.eps) || (A < 0.f && rho < 1.f - a.eps);
+  surr += fminf(rho * A, rc * A);
+  clip += clipped ? 1.f : 0.f;
+  return clipped ? 0.f : -rho * A / (float)a.n;
+}
+
+// Sums over a workgroup of NT threads by fixed wave and LDS trees; the totals are in threads 0 .. 63.
+template <int NT>
+__device__ __forceinline__ void ppo_block_sum(float& surr, float& clip) {
+  __shared__ float red[2][NT / 64];
+  const int tid = threadIdx.x;
+  surr = wave_sum(surr);
+  clip = wave_sum(clip);
+  if ((tid & 63) == 0) {
+    red[0][tid >> 6] = surr;
+    red[1][tid >> 6] = clip;
+  }
+  __syncthreads();
+  if (tid < 64) {
+    surr = wave_sum(tid < NT / 64 ? red[0][tid] : 0.f);
+    clip = wave_sum(tid < NT / 64 ? red[1][tid] : 0.f);
   }
 }
 
@@ -70,43 +137,61 @@ __global__ __launch_bounds__(64 * kGaeChunks) void gae_kernel(GaeArgs a) {
 // the loss is the same bits on every run.
 constexpr int kPpoThreads = 1024;
 __global__ __launch_bounds__(kPpoThreads) void ppo_clip_kernel(PpoArgs a) {
-  __shared__ float red[2][kPpoThreads / 64];
-  const int tid = threadIdx.x;
-  float s_surr = 0.f, s_clip = 0.f;
-  for (int t = tid; t < a.n; t += kPpoThreads) {
-    const float* ln = a.logp_new + (size_t)t * a.n_tokens;
-    const float* lo = a.logp_old + (size_t)t * a.n_tokens;
-    float sn = 0.f, so = 0.f;
-    for (int i = 0; i < a.n_tokens; ++i) {
-      sn += ln[i];
-      so += lo[i];
-    }
-    const float rho = expf(sn - so);
-    const float A = a.advantages[t];
-    const float rc = fminf(fmaxf(rho, 1.f - a.eps), 1.f + a.eps);
-    const bool clipped = (A > 0.f && rho > 1.f + a.eps) || (A < 0.f && rho < 1.f - a.eps);
-    s_surr += fminf(rho * A, rc * A);
-    s_clip += clipped ? 1.f : 0.f;
-    const float g = clipped ? 0.f : -rho * A / (float)a.n;
+  float surr = 0.f, clip = 0.f;
+  for (int t = threadIdx.x; t < a.n; t += kPpoThreads) {
+    const float g = ppo_action(a, t, surr, clip);
     float* dl = a.dlogp + (size_t)t * a.n_tokens;
     for (int i = 0; i < a.n_tokens; ++i) dl[i] = g;
   }
-  s_surr = wave_sum(s_surr);
-  s_clip = wave_sum(s_clip);
-  if ((tid & 63) == 0) {
-    red[0][tid >> 6] = s_surr;
-    red[1][tid >> 6] = s_clip;
+  ppo_block_sum<kPpoThreads>(surr, clip);
+  if (threadIdx.x == 0) {
+    a.stats[0] = -surr / (float)a.n;
+    a.stats[1] = clip / (float)a.n;
   }
-  __syncthreads();
-  if (tid < 64) {
-    float u = tid < kPpoThreads / 64 ? red[0][tid] : 0.f;
-    float c = tid < kPpoThreads / 64 ? red[1][tid] : 0.f;
-    u = wave_sum(u);
-    c = wave_sum(c);
-    if (tid == 0) {
-      a.stats[0] = -u / (float)a.n;
-      a.stats[1] = c / (float)a.n;
+}
+
+// The same over many workgroups, each a contiguous run of `per` actions (bound by one workgroup's load latency per
+// pass of 1024 actions otherwise: 65536 actions 417 -> 10 us, 4096 actions 21.1 -> 7.6).  The entry point takes no scratch, so a workgroup
+// leaves its sums, and the gradient that belongs there, in the first three token gradients of its first action
+// (n_tokens >= 3); ppo_finish_kernel adds the sums in order and puts that action's gradient in place.  An action's
+// inputs are read by its own thread before any of its gradients is written, as in the one-workgroup kernel.
+constexpr int kPpoSplitThreads = 256;
+__global__ __launch_bounds__(kPpoSplitThreads) void ppo_split_kernel(PpoArgs a, int per) {
+  const int t0 = blockIdx.x * per, t1 = min(a.n, t0 + per), tid = threadIdx.x;
+  float surr = 0.f, clip = 0.f, g0 = 0.f;
+  for (int t = t0 + tid; t < t1; t += kPpoSplitThreads) {
+    const float g = ppo_action(a, t, surr, clip);
+    if (t == t0) {
+      g0 = g;
+      continue;
     }
+    float* dl = a.dlogp + (size_t)t * a.n_tokens;
+    for (int i = 0; i < a.n_tokens; ++i) dl[i] = g;
+  }
+  ppo_block_sum<kPpoSplitThreads>(surr, clip);
+  if (tid == 0) {
+    float* dl = a.dlogp + (size_t)t0 * a.n_tokens;
+    dl[0] = surr;
+    dl[1] = clip;
+    dl[2] = g0;
+  }
+}
+
+constexpr int kPpoMaxSplit = 1024;  // workgroups of ppo_split_kernel: one thread of ppo_finish_kernel each
+__global__ __launch_bounds__(kPpoMaxSplit) void ppo_finish_kernel(PpoArgs a, int per, int groups) {
+  const int b = threadIdx.x;
+  float surr = 0.f, clip = 0.f;
+  if (b < groups) {
+    float* dl = a.dlogp + (size_t)b * per * a.n_tokens;
+    surr = dl[0];
+    clip = dl[1];
+    const float g = dl[2];
+    for (int i = 0; i < a.n_tokens; ++i) dl[i] = g;
+  }
+  ppo_block_sum<kPpoMaxSplit>(surr, clip);
+  if (b == 0) {
+    a.stats[0] = -surr / (float)a.n;
+    a.stats[1] = clip / (float)a.n;
   }
 }
 
@@ -144,6 +229,52 @@ __global__ __launch_bounds__(256) void logprob_backward_kernel(LogprobBwdArgs a)
   }
 }
 
+// The same with 16 lanes per row and float4 loads and stores (bins % 4 == 0, 16-byte aligned rows): 4 KB of logits in
+// flight per wave, 4-step trees for four rows at once where the kernel above runs 6-step ones for one, and z / T - max / T
+// as one fused multiply-add with 1 / T where it divides (the division's and expf's instructions, not memory, bounded it:
+// 458752 x 256 305 us = 3.1 TB/s -> 157 us = 6.0 TB/s).
+__global__ __launch_bounds__(256) void logprob_backward4_kernel(LogprobBwdArgs a) {
+  const int row = blockIdx.x * 16 + (threadIdx.x >> 4);
+  const int l = threadIdx.x & 15, lim4 = a.bins / 4;
+  const bool in = row < a.rows;
+  const float4* z = reinterpret_cast<const float4*>(a.logits + (size_t)(in ? row : 0) * a.bins);
+  const float inv_t = 1.f / a.temperature;
+  float v[4][4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const float4 q = l + 16 * u < lim4 ? z[l + 16 * u] : make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
+    v[u][0] = q.x; v[u][1] = q.y; v[u][2] = q.z; v[u][3] = q.w;
+  }
+  const int tok = a.tokens[in ? row : 0];
+  const float dl = a.dlogp[in ? row : 0];
+  float m = -INFINITY;
+#pragma unroll
+  for (int u = 0; u < 4; ++u) m = fmaxf(m, fmaxf(fmaxf(v[u][0], v[u][1]), fmaxf(v[u][2], v[u][3])));
+  m = group16_max(m);
+  const float mt = m * inv_t;
+  float su[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const bool live = l + 16 * u < lim4;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[u][e] = live ? expf(fmaf(v[u][e], inv_t, -mt)) : 0.f;
+    su[u] = (v[u][0] + v[u][1]) + (v[u][2] + v[u][3]);
+  }
+  const float se = group16_sum((su[0] + su[1]) + (su[2] + su[3]));
+  const int k = tok - a.action_begin;
+  const float g = (k >= 0 && k < a.bins) ? dl / a.temperature : __builtin_nanf("");
+  const float inv = 1.f / se;
+  if (!in) return;
+  float4* dz = reinterpret_cast<float4*>(a.dlogits + (size_t)row * a.bins);
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const int j = 4 * (l + 16 * u);
+    if (j < a.bins)
+      dz[l + 16 * u] = make_float4(g * ((j == k ? 1.f : 0.f) - v[u][0] * inv), g * ((j + 1 == k ? 1.f : 0.f) - v[u][1] * inv),
+                                   g * ((j + 2 == k ? 1.f : 0.f) - v[u][2] * inv), g * ((j + 3 == k ? 1.f : 0.f) - v[u][3] * inv));
+  }
+}
+
 }  // namespace
 
 hipError_t launch_gae(const GaeArgs& a, hipStream_t s) {
@@ -154,14 +285,27 @@ hipError_t launch_gae(const GaeArgs& a, hipStream_t s) {
 
 hipError_t launch_ppo_clip(const PpoArgs& a, hipStream_t s) {
   if (a.n <= 0) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(ppo_clip_kernel, dim3(1), dim3(kPpoThreads), 0, s, a);
+  // One workgroup while it makes one pass (a second launch costs 3 us, each further pass about 5); and below 3 tokens, where an
+  // action's gradients have no room for a workgroup's sums.
+  if (a.n <= kPpoThreads || a.n_tokens < 3) {
+    hipLaunchKernelGGL(ppo_clip_kernel, dim3(1), dim3(kPpoThreads), 0, s, a);
+  } else {
+    const int per = std::max(kPpoSplitThreads, (a.n + kPpoMaxSplit - 1) / kPpoMaxSplit), groups = (a.n + per - 1) / per;
+    hipLaunchKernelGGL(ppo_split_kernel, dim3(groups), dim3(kPpoSplitThreads), 0, s, a, per);
+    hipLaunchKernelGGL(ppo_finish_kernel, dim3(1), dim3(kPpoMaxSplit), 0, s, a, per, groups);
+  }
   return hipGetLastError();
 }
 
 hipError_t launch_logprob_backward(const LogprobBwdArgs& a, hipStream_t s) {
   if (a.rows <= 0) return hipSuccess;
   if (a.bins <= 0 || a.bins > 256) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(logprob_backward_kernel, dim3((a.rows + 3) / 4), dim3(256), 0, s, a);
+  // float4 rows, and a temperature whose reciprocal is a normal number far from the ends of the range
+  const uintptr_t align = reinterpret_cast<uintptr_t>(a.logits) | reinterpret_cast<uintptr_t>(a.dlogits);
+  if (a.bins % 4 == 0 && align % 16 == 0 && a.temperature >= 0x1p-100f && a.temperature <= 0x1p100f)
+    hipLaunchKernelGGL(logprob_backward4_kernel, dim3((a.rows + 15) / 16), dim3(256), 0, s, a);
+  else
+    hipLaunchKernelGGL(logprob_backward_kernel, dim3((a.rows + 3) / 4), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 

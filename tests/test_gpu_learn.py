@@ -111,6 +111,17 @@ def test_ppo_clip_matches_oracle(n, k, spread):
     _ppo_check(n, k, 0.2, seed=n + k, spread=spread, adv_zero_frac=0.01)
 
 
+@pytest.mark.parametrize("n,k", [(1024, 7), (1025, 7), (1280, 3), (1281, 4), (2000, 2), (262145, 3), (300000, 16)])
+def test_ppo_clip_over_many_workgroups(n, k):
+    """Either side of one workgroup's range, whole and nearly empty last workgroups, too few tokens to split, more
+    actions than 1024 workgroups of 256; and gradients written over the new log-probs."""
+    _, g = _ppo_check(n, k, 0.2, seed=n + k, spread=0.05, adv_zero_frac=0.01)
+    old, new, adv = [torch.from_numpy(x).cuda() for x in inputs.ppo_minibatch(n, k, seed=n + k, spread=0.05)]
+    adv[: int(n * 0.01)] = 0.0
+    vla.ppo_clip(new, old, adv, 0.2, dlogp=new)
+    assert np.array_equal(new.cpu().numpy(), g)
+
+
 def test_ppo_ratio_one_at_the_old_policy():
     """logp_new == logp_old: rho = 1 exactly, nothing clipped, loss = -mean A
     and every token's gradient is -A / n (one fp32 rounding)."""
@@ -154,6 +165,24 @@ def _bwd_check(rows, bins, T, seed, bad_row=None):
 @pytest.mark.parametrize("rows,bins", [(896, 256), (5, 100), (1, 1), (3, 255)])
 def test_logprob_backward_matches_oracle(rows, bins):
     _bwd_check(rows, bins, 1.5, seed=rows + bins)
+
+
+@pytest.mark.parametrize("rows,bins", [(1, 4), (15, 60), (17, 64), (33, 68), (16, 200), (47, 252), (31, 256)])
+def test_logprob_backward_of_whole_float4_rows(rows, bins):
+    """Rows of whole float4s around the 16 rows of a workgroup; the same values where the rows are not 16-byte aligned
+    (the other kernel), and with masked (-inf) logits."""
+    _bwd_check(rows, bins, 0.7, seed=rows + bins)
+    rng = np.random.default_rng(rows)
+    z = rng.normal(size=(rows, bins)).astype(np.float32)
+    z[:, 1:3] = -np.inf
+    tok, dl = np.zeros(rows, np.int32), np.ones(rows, np.float32)
+    zt, kt, dt = [torch.from_numpy(x).cuda() for x in (z, tok, dl)]
+    got = vla.logprob_backward(zt, kt, 0, 0.7, dt).cpu().numpy()
+    odd = torch.empty(rows * bins + 1, device="cuda")[1:].view(rows, bins)
+    other = vla.logprob_backward(odd.copy_(zt), kt, 0, 0.7, dt).cpu().numpy()
+    ref = lo.logprob_grad(z, tok, 0, 0.7, dl)
+    for x in (got, other):
+        assert np.all(x[:, 1:3] == 0) and np.all(np.abs(x - ref) <= 32 * U32 * (1 / 0.7 + np.abs(ref)))
 
 
 def test_logprob_backward_out_of_range_token_gives_a_nan_row():
