@@ -252,99 +252,160 @@ __global__ __launch_bounds__(512, 1) void attn_prefill_kernel(PrefillAttnArgs a)
   }
 }
 
+// One 256-thread workgroup per (environment, head).  Scores: HD / 8 lanes per key row, KPP keys a pass.  P V: thread
+// (feature, group of pages).
+//
+// The work is 150 KB of reads and almost no arithmetic.  With few workgroups what counts is that the reads do not wait on
+// each other: KP passes of K rows and VP pages of V go into registers before the token's own q, k, v have been summed
+// from the QKV projection's partials (all of a sequence with KP = NK, VP = NV), the rest KC passes and VC pages at a time.
+// With many, the workgroups of a CU cover each other's waits, and registers that limit their number cost more (the rule
+// is in launch_attn_decode).
+// The order of every sum depends on the sequence length alone.
 template <int HD>
+struct DecodeShape {
+  static constexpr int LPK = HD / 8;                  // lanes per key row
+  static constexpr int KPP = 256 / LPK;               // keys per pass
+  static constexpr int G = 256 / HD;                  // page groups in P*V
+  static constexpr int NK = kMaxKeys / KPP, NV = kMaxPages / G;
+};
+
+// Sum over the LPK lanes of a key row: xor 8 (16 lanes), 4, 2, 1.
+template <int LPK>
+__device__ __forceinline__ float key_sum(float v) {
+  if constexpr (LPK == 16) return row_sum16(v);
+  v += dpp_mov<0x114, 0xA>(dpp_mov<0x104, 0x5>(v, v), v);  // xor 4: row_shl 4 into even banks, row_shr 4 into odd ones
+  v += dpp_mov<0x4E>(v, v);                                // quad_perm 2 3 0 1
+  return v + dpp_mov<0xB1>(v, v);                          // quad_perm 1 0 3 2
+}
+
+template <int HD, int KP, int VP, int KC, int VC>
 __global__ __launch_bounds__(256) void attn_decode_kernel(DecodeAttnArgs a) {
-  constexpr int LPK = HD / 8;          // lanes per key row
-  constexpr int KPP = 256 / LPK;       // keys per pass
-  constexpr int G = 256 / HD;          // feature groups in P*V
-  constexpr int HALF = HD / 2;
-  __shared__ float sc[kMaxKeys];
-  __shared__ float qs[HD], kn[HD], vn[HD];  // this token's rotated q, k and its v (bf16 values)
-  __shared__ float red[4];
+  using S = DecodeShape<HD>;
+  constexpr int LPK = S::LPK, KPP = S::KPP, G = S::G, HALF = HD / 2;
+  __shared__ __attribute__((aligned(16))) float sc[kMaxKeys];
+  __shared__ __attribute__((aligned(16))) bf16_t q16[HD], k16[HD];  // this token's rotated q and k
+  __shared__ float vn[HD];                                           // and its v (a bf16 value)
+  __shared__ float red[2][4];
   __shared__ float op[G][HD];
-  __shared__ int ptl[kMaxPages];  // the environment's page table
   const int head = blockIdx.x, b = blockIdx.y;
   const int H = a.n_heads, tid = threadIdx.x;
-  const int n = a.env_prefix[b] + a.step;  // keys 0 .. n-1; key n-1 is this step's token
-  const int pos = n - 1;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int pos = a.env_prefix[b] + a.step - 1;  // this step's token; the keys are 0 .. pos
+  const int n = pos + 1, last = pos / kPage;
   const int32_t* pt = a.page_table + b * a.max_pages;
-  if (tid < a.max_pages) ptl[tid] = pt[tid];
 
   // ---- q, k, v of the token for this head: one thread per rotary pair of
   // q and k (columns permuted per head as for the prefill GEMM's epilogue:
   // pair (32 blk + c, HALF + 32 blk + c) sits in columns 64 blk + c and
-  // 64 blk + c + 32 of the head) and per pair of v features (e, e + HALF)
-  if (tid < 3 * HALF) {
-    const int region = tid / HALF, e = tid % HALF;
-    const int N = 3 * a.d;
-    int col1, col2;
-    if (region < 2) {
-      col1 = region * a.d + head * HD + 64 * (e / 32) + e % 32;
-      col2 = col1 + 32;
-    } else {
-      col1 = 2 * a.d + head * HD + e;
-      col2 = col1 + HALF;
+  // 64 blk + c + 32 of the head) and per pair of v features (e, e + HALF).
+  // Their partials are loaded ahead of the pages.
+  const bool qkv = tid < 3 * HALF;
+  const int region = tid / HALF, e = tid % HALF, N = 3 * a.d;
+  float p1[kSlotsAhead], p2[kSlotsAhead];
+  float2 cs = make_float2(1.f, 0.f);
+  const float *c1 = nullptr, *c2 = nullptr;
+  int ns1 = 0, ns2 = 0;
+  const size_t stride = (size_t)a.B * N;
+  if (qkv) {
+    const int col1 = region * a.d + head * HD + (region < 2 ? 64 * (e / 32) + e % 32 : e);
+    const int col2 = col1 + (region < 2 ? 32 : HALF);
+    ns1 = skinny_slots(a.plan, col1 >> 6);
+    ns2 = skinny_slots(a.plan, col2 >> 6);
+    c1 = a.part + (size_t)b * N + col1;
+    c2 = a.part + (size_t)b * N + col2;
+#pragma unroll
+    for (int s = 0; s < kSlotsAhead; ++s) {
+      if (s < ns1) p1[s] = c1[s * stride];
+      if (s < ns2) p2[s] = c2[s * stride];
     }
-    const float x1 = skinny_sum(a.part, a.plan, a.B, N, b, col1);
-    const float x2 = skinny_sum(a.part, a.plan, a.B, N, b, col2);
-    const int page = pt[pos / kPage], slot = pos % kPage;
+    if (region < 2) cs = a.rope[pos * HALF + e];
+  }
+
+  // ---- the pages (past the last one, it again: nothing of those is used); a wave's keys of a pass lie in one page
+  const int key0 = tid / LPK, part = tid % LPK;
+  const int i = tid % HD, grp = __builtin_amdgcn_readfirstlane(tid / HD);
+  auto k_row = [&](int it) {  // this lane's 8 features of key KPP it + key0
+    const int page = pt[min(KPP / kPage * it + wave * (64 / LPK) / kPage, last)];
+    return *reinterpret_cast<const uint4*>(a.kv.k + (((size_t)page * H + head) * kPage + key0 % kPage) * HD + part * 8);
+  };
+  auto v_page = [&](int it, uint4 (&v)[2]) {  // the 16 keys of page grp + G it for feature i
+    const uint4* vp = reinterpret_cast<const uint4*>(a.kv.v + (((size_t)pt[min(grp + G * it, last)] * H + head) * HD + i) * kPage);
+    v[0] = vp[0];
+    v[1] = vp[1];
+  };
+  uint4 kf[KP > 0 ? KP : 1], vf[VP > 0 ? VP : 1][2];
+#pragma unroll
+  for (int it = 0; it < KP; ++it) kf[it] = k_row(it);
+#pragma unroll
+  for (int it = 0; it < VP; ++it) v_page(it, vf[it]);
+  __builtin_amdgcn_sched_barrier(0);  // the loads above go out before the first wait
+
+  if (qkv) {
+    float x1 = 0.f, x2 = 0.f;  // as skinny_sum: slots added in order
+#pragma unroll
+    for (int s = 0; s < kSlotsAhead; ++s) {
+      if (s < ns1) x1 += p1[s];
+      if (s < ns2) x2 += p2[s];
+    }
+    for (int s = kSlotsAhead; s < ns1; ++s) x1 += c1[s * stride];
+    for (int s = kSlotsAhead; s < ns2; ++s) x2 += c2[s * stride];
+    const size_t at = (size_t)pt[last] * H + head;
+    const int slot = pos % kPage;
     if (region == 2) {
       const bf16_t v1 = f2bf(x1), v2 = f2bf(x2);
-      bf16_t* vb = a.kv.v + ((size_t)page * H + head) * HD * kPage + slot;
+      bf16_t* vb = a.kv.v + at * HD * kPage + slot;
       vb[(size_t)e * kPage] = v1;
       vb[(size_t)(e + HALF) * kPage] = v2;
       vn[e] = bf2f(v1);
       vn[e + HALF] = bf2f(v2);
     } else {
-      const float2 cs = a.rope[pos * HALF + e];
-      const bf16_t r1 = f2bf(x1 * cs.x - x2 * cs.y), r2 = f2bf(x1 * cs.y + x2 * cs.x);
-      if (region == 0) {
-        qs[e] = bf2f(r1);
-        qs[e + HALF] = bf2f(r2);
-      } else {
-        bf16_t* kr = a.kv.k + (((size_t)page * H + head) * kPage + slot) * HD;
+      // the fused multiply-adds of the prefill GEMM's epilogue
+      const bf16_t r1 = f2bf(fmaf(x1, cs.x, -(x2 * cs.y))), r2 = f2bf(fmaf(x2, cs.x, x1 * cs.y));
+      bf16_t* t16 = region == 0 ? q16 : k16;
+      t16[e] = r1;
+      t16[e + HALF] = r2;
+      if (region == 1) {
+        bf16_t* kr = a.kv.k + (at * kPage + slot) * HD;
         kr[e] = r1;
         kr[e + HALF] = r2;
-        kn[e] = bf2f(r1);
-        kn[e + HALF] = bf2f(r2);
       }
     }
   }
   __syncthreads();
 
-  const int part = tid % LPK;
+  // ---- scores: one key row per LPK lanes
   float qv[8];
-#pragma unroll
-  for (int j = 0; j < 8; ++j) qv[j] = qs[part * 8 + j];
-  // scores: one key row per LPK lanes
-  for (int base = 0; base < n; base += KPP) {
-    const int key = base + tid / LPK;
+  unpack8(*reinterpret_cast<const uint4*>(q16 + part * 8), qv);
+  auto score = [&](int it, uint4 kr) {
+    const int key = KPP * it + key0;
+    if (KPP * (it + 1) > pos && key == pos) kr = *reinterpret_cast<const uint4*>(k16 + part * 8);  // this step's token
+    float kv8[8];
+    unpack8(kr, kv8);
     float acc = 0.f;
-    if (key < n) {
-      float kf[8];
-      if (key < pos) {
-        const bf16_t* kp = a.kv.k + (((size_t)ptl[key / kPage] * H + head) * kPage + key % kPage) * HD + part * 8;
-        unpack8(*reinterpret_cast<const uint4*>(kp), kf);
-      } else {  // this step's token
 #pragma unroll
-        for (int j = 0; j < 8; ++j) kf[j] = kn[part * 8 + j];
-      }
-#pragma unroll
-      for (int j = 0; j < 8; ++j) acc += qv[j] * kf[j];
-    }
-#pragma unroll
-    for (int o = LPK / 2; o > 0; o >>= 1) acc += __shfl_xor(acc, o, kWave);
+    for (int j = 0; j < 8; ++j) acc += qv[j] * kv8[j];
+    acc = key_sum<LPK>(acc);
     if (part == 0 && key < n) sc[key] = acc * a.scale;
+  };
+#pragma unroll
+  for (int it = 0; it < KP; ++it)
+    if (KPP * it < n) score(it, kf[it]);
+  for (int it = KP; KPP * it < n; it += KC) {
+    uint4 kc[KC];
+#pragma unroll
+    for (int u = 0; u < KC; ++u) kc[u] = k_row(it + u);
+#pragma unroll
+    for (int u = 0; u < KC; ++u)
+      if (KPP * (it + u) < n) score(it + u, kc[u]);
   }
   __syncthreads();
 
   float m = -INFINITY;
   for (int t = tid; t < n; t += 256) m = fmaxf(m, sc[t]);
   m = wave_max(m);
-  if ((tid & 63) == 0) red[tid >> 6] = m;
+  if ((tid & 63) == 0) red[0][wave] = m;
   __syncthreads();
-  m = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
-  __syncthreads();
+  m = fmaxf(fmaxf(red[0][0], red[0][1]), fmaxf(red[0][2], red[0][3]));
   float s = 0.f;
   for (int t = tid; t < n; t += 256) {
     const float p = expf(sc[t] - m);
@@ -352,22 +413,41 @@ __global__ __launch_bounds__(256) void attn_decode_kernel(DecodeAttnArgs a) {
     s += p;
   }
   s = wave_sum(s);
-  if ((tid & 63) == 0) red[tid >> 6] = s;
+  if ((tid & 63) == 0) red[1][wave] = s;
   __syncthreads();
-  s = red[0] + red[1] + red[2] + red[3];
+  s = red[1][0] + red[1][1] + red[1][2] + red[1][3];
 
-  const int i = tid % HD, grp = tid / HD;
   const float vnew = vn[i];
   float acc = 0.f;
-  for (int pg = grp; pg * kPage < n; pg += G) {
-    const bf16_t* vp = a.kv.v + (((size_t)ptl[pg] * H + head) * HD + i) * kPage;
-    float vf[16];
-    unpack8(*reinterpret_cast<const uint4*>(vp), vf);
-    unpack8(*reinterpret_cast<const uint4*>(vp + 8), vf + 8);
-    const int lim = min(kPage, n - pg * kPage);
+  auto pv = [&](int it, const uint4 (&v)[2]) {
+    const int pg = grp + G * it;
+    float v16[16], p16[16];
+    unpack8(v[0], v16);
+    unpack8(v[1], v16 + 8);
 #pragma unroll
-    for (int j = 0; j < kPage; ++j)
-      if (j < lim) acc += sc[pg * kPage + j] * (pg * kPage + j == pos ? vnew : vf[j]);  // the token's v from LDS
+    for (int j = 0; j < 4; ++j) {
+      const float4 p = *reinterpret_cast<const float4*>(sc + pg * kPage + 4 * j);
+      p16[4 * j] = p.x; p16[4 * j + 1] = p.y; p16[4 * j + 2] = p.z; p16[4 * j + 3] = p.w;
+    }
+    if (pg < last) {
+#pragma unroll
+      for (int j = 0; j < kPage; ++j) acc += p16[j] * v16[j];
+    } else {  // the token's v from LDS; slots past it hold no key
+#pragma unroll
+      for (int j = 0; j < kPage; ++j)
+        if (pg * kPage + j <= pos) acc += p16[j] * (pg * kPage + j == pos ? vnew : v16[j]);
+    }
+  };
+#pragma unroll
+  for (int it = 0; it < VP; ++it)
+    if (grp + G * it <= last) pv(it, vf[it]);
+  for (int it = VP; grp + G * it <= last; it += VC) {
+    uint4 vc[VC][2];
+#pragma unroll
+    for (int u = 0; u < VC; ++u) v_page(it + u, vc[u]);
+#pragma unroll
+    for (int u = 0; u < VC; ++u)
+      if (grp + G * (it + u) <= last) pv(it + u, vc[u]);
   }
   op[grp][i] = acc;
   __syncthreads();
@@ -480,12 +560,32 @@ hipError_t launch_attn_prefill(const PrefillAttnArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
+namespace {
+template <int HD, int KP, int VP, int KC, int VC>
+void launch_decode(const DecodeAttnArgs& a, hipStream_t s) {
+  hipLaunchKernelGGL((attn_decode_kernel<HD, KP, VP, KC, VC>), dim3(a.n_heads, a.B), dim3(256), 0, s, a);
+}
+}  // namespace
+
 hipError_t launch_attn_decode(const DecodeAttnArgs& a, hipStream_t s) {
   if (a.B <= 0) return hipSuccess;
-  const dim3 grid(a.n_heads, a.B), block(256);
-  if (a.head_dim == 128) hipLaunchKernelGGL(attn_decode_kernel<128>, grid, block, 0, s, a);
-  else if (a.head_dim == 64) hipLaunchKernelGGL(attn_decode_kernel<64>, grid, block, 0, s, a);
-  else return hipErrorInvalidValue;
+  if (a.max_pages < 1 || a.max_pages > kMaxPages) return hipErrorInvalidValue;
+  if (a.head_dim != 128 && a.head_dim != 64) return hipErrorInvalidValue;
+  // By workgroups per CU, which is what covers a workgroup's waits (us, all of a sequence ahead / 4 passes and 2 pages
+  // at a time / one by one; a workgroup that looked up its pages in LDS and read one by one before): head_dim 128, at
+  // most one per CU 11.1 / 14.9 / 19.9 (28.0), 2 22.2 / 19.7 / 25.6, 4 42.4 / 32.7 / 34.6, 8 75 / 69.7 / 60.7 (59.0);
+  // head_dim 64, one 8.9 / 10.9 / 11.8 (19.2), 4 19.7 / 17.5 / 17.2, 8 41.9 / 37.4 / 32.7.
+  const long long wgs = (long long)a.B * a.n_heads;
+  const bool few = wgs <= a.cus, some = wgs <= 4ll * a.cus;
+  if (a.head_dim == 128) {
+    if (few) launch_decode<128, DecodeShape<128>::NK, DecodeShape<128>::NV, 1, 1>(a, s);
+    else if (some) launch_decode<128, 0, 0, 4, 2>(a, s);
+    else launch_decode<128, 0, 0, 1, 1>(a, s);
+  } else {
+    if (few) launch_decode<64, DecodeShape<64>::NK, DecodeShape<64>::NV, 1, 1>(a, s);
+    else if (some) launch_decode<64, 0, 0, 4, 2>(a, s);
+    else launch_decode<64, 0, 0, 1, 1>(a, s);
+  }
   return hipGetLastError();
 }
 

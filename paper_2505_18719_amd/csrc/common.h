@@ -35,28 +35,37 @@ __device__ __forceinline__ void unpack8(const uint4& v, float* f) {
   }
 }
 
+// v of another lane (DPP control CTRL); banks of 4 lanes outside BANKS keep `old`.
+template <int CTRL, int BANKS = 0xF>
+__device__ __forceinline__ float dpp_mov(float old, float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(old), __float_as_int(v), CTRL, 0xF, BANKS, false));
+}
+
+// Sum / max over the 16 lanes that share (lane / 16), by rotations of 8, 4, 2, 1: with what the steps before have made
+// equal, the partners (and so the bits) of the butterfly over lane ^ 8, 4, 2, 1, without its trips through LDS hardware.
+__device__ __forceinline__ float row_sum16(float v) {
+  v += dpp_mov<0x128>(v, v);
+  v += dpp_mov<0x124>(v, v);
+  v += dpp_mov<0x122>(v, v);
+  return v + dpp_mov<0x121>(v, v);
+}
+__device__ __forceinline__ float row_max16(float v) {
+  v = fmaxf(v, dpp_mov<0x128>(v, v));
+  v = fmaxf(v, dpp_mov<0x124>(v, v));
+  v = fmaxf(v, dpp_mov<0x122>(v, v));
+  return fmaxf(v, dpp_mov<0x121>(v, v));
+}
+
+// Sum / max over the wave: lane ^ 32, 16, then as above.
 __device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
-  return v;
+  v += __shfl_xor(v, 32, kWave);
+  v += __shfl_xor(v, 16, kWave);
+  return row_sum16(v);
 }
-
 __device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, kWave));
-  return v;
-}
-
-// Sum / max over the 16 lanes that share (lane / 16).
-__device__ __forceinline__ float group16_sum(float v) {
-#pragma unroll
-  for (int o = 8; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
-  return v;
-}
-__device__ __forceinline__ float group16_max(float v) {
-#pragma unroll
-  for (int o = 8; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, kWave));
-  return v;
+  v = fmaxf(v, __shfl_xor(v, 32, kWave));
+  v = fmaxf(v, __shfl_xor(v, 16, kWave));
+  return row_max16(v);
 }
 
 __device__ __forceinline__ f32x4 mfma16(const bf16x8& a, const bf16x8& b, const f32x4& c) {

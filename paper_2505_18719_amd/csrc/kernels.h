@@ -235,6 +235,7 @@ struct DecodeAttnArgs {
   int step;  // 1-based decode step: token position = env_prefix[b] + step - 1
   int B, d, n_heads, head_dim;
   float scale;
+  int cus;  // compute units of the device
 };
 hipError_t launch_attn_decode(const DecodeAttnArgs& a, hipStream_t s);
 

@@ -250,7 +250,7 @@ __global__ __launch_bounds__(256) void logprob_backward4_kernel(LogprobBwdArgs a
   float m = -INFINITY;
 #pragma unroll
   for (int u = 0; u < 4; ++u) m = fmaxf(m, fmaxf(fmaxf(v[u][0], v[u][1]), fmaxf(v[u][2], v[u][3])));
-  m = group16_max(m);
+  m = row_max16(m);
   const float mt = m * inv_t;
   float su[4];
 #pragma unroll
@@ -260,7 +260,7 @@ __global__ __launch_bounds__(256) void logprob_backward4_kernel(LogprobBwdArgs a
     for (int e = 0; e < 4; ++e) v[u][e] = live ? expf(fmaf(v[u][e], inv_t, -mt)) : 0.f;
     su[u] = (v[u][0] + v[u][1]) + (v[u][2] + v[u][3]);
   }
-  const float se = group16_sum((su[0] + su[1]) + (su[2] + su[3]));
+  const float se = row_sum16((su[0] + su[1]) + (su[2] + su[3]));
   const int k = tok - a.action_begin;
   const float g = (k >= 0 && k < a.bins) ? dl / a.temperature : __builtin_nanf("");
   const float inv = 1.f / se;

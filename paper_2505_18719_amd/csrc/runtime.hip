@@ -328,7 +328,7 @@ int decode_step_fused(vla_model* m, int B, int step, unsigned& bar_base, hipStre
     for (int l = 0; l < D.L; ++l) {
       const LayerW& w = m->lw[l];
       DecodeAttnArgs da{m->part_nx, m->plan_qkv, m->rope, o, m->kv[l], ptab, D.max_pages, eprefix,
-                        step, rows, D.d, D.H, D.hd, m->scale};
+                        step, rows, D.d, D.H, D.hd, m->scale, m->cus};
       PROF_LAUNCH(VLA_PROF_DECODE_ATTN, kv_bytes, launch_attn_decode(da, s));
       const bool last = l + 1 == D.L;
       DecodeLayerArgs a{};
@@ -956,7 +956,7 @@ int vla_decode_actions(vla_model* m, int32_t B, const float* gumbel, float T, in
           SkinnyArgs sq{u, rows, w.wqkv, 3 * D.d, D.d, m->part};
           PROF_LAUNCH(VLA_PROF_DECODE_GEMM, skinny_bytes(3.0 * D.d, D.d, rows), launch_skinny(sq, m->plan_qkv, s));
           DecodeAttnArgs da{m->part, m->plan_qkv, m->rope, u, m->kv[l], ptab, D.max_pages, eprefix,
-                            i, rows, D.d, D.H, D.hd, m->scale};
+                            i, rows, D.d, D.H, D.hd, m->scale, m->cus};
           PROF_LAUNCH(VLA_PROF_DECODE_ATTN, kv_bytes, launch_attn_decode(da, s));
           SkinnyArgs so{u, rows, w.wo, D.d, D.d, m->part};
           PROF_LAUNCH(VLA_PROF_DECODE_GEMM, skinny_bytes(D.d, D.d, rows), launch_skinny(so, m->plan_o, s));

@@ -52,6 +52,34 @@ def test_persistent_decode_matches_the_per_kernel_path_bitwise(name):
     S.model.close()
 
 
+@pytest.mark.parametrize("head_dim", [64, 128])
+def test_decode_attention_variants_give_the_same_bits(head_dim):
+    """An environment decodes to the same bits alone, among 30 and among 128 of 16 heads: the decode attention's variants
+    for at most one workgroup per CU, at most four, and more.  Sequences end at the first and last slot of a page and at
+    the longest length."""
+    lens = np.array([0, 57, 9, 16, 15, 1, 40, 33, 25, 56] + [(7 * i) % 58 for i in range(118)], dtype=np.int32)
+    cfg = inputs.TINY.replace(name=f"hd{head_dim}", n_layers=1, d_model=16 * head_dim, n_heads=16, batch=128,
+                              prompt_min=0, prompt_max=57)
+    S = Setup(cfg, seed=13)
+    inp, dev = S.inputs(seed=13, prompt_lens=lens)
+    off = np.concatenate([[0], np.cumsum(inp.prompt_lens)])
+
+    def run(a, b):
+        S.model.prefill(dev["vis"][a:b].contiguous(), dev["ids"][off[a]:off[b]].contiguous(), inp.prompt_lens[a:b])
+        out = S.model.decode_actions(dev["gumbel"][a:b].contiguous(), 1.5)
+        torch.cuda.synchronize()
+        return {k: v.clone() for k, v in out.items()}
+
+    full, some = run(0, 128), run(0, 30)
+    for k in full:
+        assert torch.equal(full[k][:30], some[k]), k
+    for b in range(10):
+        one = run(b, b + 1)
+        for k in full:
+            assert torch.equal(full[k][b], one[k][0]), (k, b)
+    S.model.close()
+
+
 def test_persistent_decode_repeats_bit_exactly():
     S = Setup(inputs.L7B_B64.replace(n_layers=2), seed=12)
     S.model.debug_decode_path(1)
