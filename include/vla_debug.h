@@ -17,8 +17,9 @@ extern "C" {
  * frag layout (vla_debug_pack_frag).  Requires K % 32 == 0, N % 64 == 0. */
 int vla_debug_gemm(const void* A, const void* W, int32_t M, int32_t N, int32_t K, float* C, void* stream);
 
-/* vla_debug_gemm on one of the GEMM's tile shapes, 0 .. 8 (0: 256 x 256, the others smaller; -1: the shape the
- * library picks for these sizes, as vla_debug_gemm).  Every shape gives the same bits. */
+/* vla_debug_gemm on one of the GEMM's tile shapes, 0 .. 8 (0: 256 x 256, the others smaller), or cut in two: the first
+ * 256 columns on shape 0 and the rest on shape 1 .. 8 (9 .. 16), or the first 256 rows (17 .. 24); a cut that leaves no
+ * rest is refused.  -1: the plan the library picks for these sizes, as vla_debug_gemm.  All give the same bits. */
 int vla_debug_gemm_shape(const void* A, const void* W, int32_t M, int32_t N, int32_t K, int32_t shape, float* C,
                          void* stream);
 

@@ -45,7 +45,8 @@ extern "C" {
 
 int vla_debug_gemm_shape(const void* A, const void* W, int32_t M, int32_t N, int32_t K, int32_t shape, float* C,
                          void* stream) {
-  if (!A || !W || !C || M < 0 || N < 0 || K <= 0 || shape < -1 || shape >= kGemmShapes) return VLA_EINVAL;
+  if (!A || !W || !C || M < 0 || N < 0 || K <= 0 || shape < -1 || shape > 2 * (kGemmShapes - 1) + kGemmShapes - 1)
+    return VLA_EINVAL;
   GemmArgs g{};
   g.A = static_cast<const bf16_t*>(A);
   g.W = static_cast<const bf16_t*>(W);
@@ -54,7 +55,17 @@ int vla_debug_gemm_shape(const void* A, const void* W, int32_t M, int32_t N, int
   g.K = K;
   g.C = C;
   g.ldc = N;
-  return launch_gemm(g, kEpiStoreF32, static_cast<hipStream_t>(stream), shape) == hipSuccess ? VLA_OK : VLA_EHIP;
+  hipStream_t s = static_cast<hipStream_t>(stream);
+  if (shape < 0) return launch_gemm(g, kEpiStoreF32, s) == hipSuccess ? VLA_OK : VLA_EHIP;
+  GemmPlan p{shape, 0, 0, 0};
+  if (shape >= kGemmShapes) {
+    const int i = shape - kGemmShapes, n = kGemmShapes - 1;
+    p.first = 0;
+    p.rest = 1 + i % n;
+    p.rows = i / n ? 256 : 0;
+    p.cols = i / n ? 0 : 256;
+  }
+  return launch_gemm(g, kEpiStoreF32, s, p) == hipSuccess ? VLA_OK : VLA_EHIP;
 }
 
 int vla_debug_gemm(const void* A, const void* W, int32_t M, int32_t N, int32_t K, float* C, void* stream) {

@@ -444,16 +444,7 @@ static int persistent_workgroups() {
   return cus[dev];
 }
 
-hipError_t launch_gemm(const GemmArgs& a, GemmEpilogue epi, hipStream_t s, int shape) {
-  if (a.M <= 0 || a.N <= 0) return hipSuccess;
-  // frag-layout operands, 32-bit byte offsets into them
-  const int ka = a.ka ? a.ka : a.K, kw = a.kw ? a.kw : a.K;
-  if (a.K % BK != 0 || a.N % 64 != 0 || ka < a.K || kw < a.K || ka % 32 != 0 || kw % 32 != 0 ||
-      (long long)frag_elems(a.M, ka) * 2 >= (1ll << 31) || (long long)frag_elems(a.N, kw) * 2 >= (1ll << 31))
-    return hipErrorInvalidValue;
-  if (epi == kEpiSwiGluKeep && (!a.C || a.ldc % 4 != 0 || a.ldc < a.N)) return hipErrorInvalidValue;
-  if (shape >= kGemmShapes) return hipErrorInvalidValue;
-  if (shape < 0) shape = gemm_shape(a.M, a.N, a.K, persistent_workgroups());
+static hipError_t launch_part(const GemmArgs& a, GemmEpilogue epi, int shape, hipStream_t s) {
   if (shape > 0) return launch_gemm_shape(a, epi, shape, s);
   const int tm = (a.M + BM - 1) / BM, tn = (a.N + BN - 1) / BN;
   const dim3 grid(std::min(tm * tn, persistent_workgroups())), block(NT);
@@ -467,6 +458,50 @@ hipError_t launch_gemm(const GemmArgs& a, GemmEpilogue epi, hipStream_t s, int s
       break;
   }
   return hipGetLastError();
+}
+
+hipError_t launch_gemm(const GemmArgs& a, GemmEpilogue epi, hipStream_t s) {
+  if (a.M <= 0 || a.N <= 0) return hipSuccess;
+  return launch_gemm(a, epi, s, gemm_plan(a.M, a.N, a.K, persistent_workgroups()));
+}
+
+hipError_t launch_gemm(const GemmArgs& a, GemmEpilogue epi, hipStream_t s, const GemmPlan& p) {
+  if (a.M <= 0 || a.N <= 0) return hipSuccess;
+  // frag-layout operands, 32-bit byte offsets into them
+  const int ka = a.ka ? a.ka : a.K, kw = a.kw ? a.kw : a.K;
+  if (a.K % BK != 0 || a.N % 64 != 0 || ka < a.K || kw < a.K || ka % 32 != 0 || kw % 32 != 0 ||
+      (long long)frag_elems(a.M, ka) * 2 >= (1ll << 31) || (long long)frag_elems(a.N, kw) * 2 >= (1ll << 31))
+    return hipErrorInvalidValue;
+  if (epi == kEpiSwiGluKeep && (!a.C || a.ldc % 4 != 0 || a.ldc < a.N)) return hipErrorInvalidValue;
+  if (p.first < 0 || p.first >= kGemmShapes) return hipErrorInvalidValue;
+  if (p.rows == 0 && p.cols == 0) return launch_part(a, epi, p.first, s);
+  if (p.rows < 0 || p.cols < 0 || (p.rows && p.cols) || p.rows % 256 != 0 || p.cols % 256 != 0 || p.rows >= a.M ||
+      p.cols >= a.N || p.rest < 1 || p.rest >= kGemmShapes)
+    return hipErrorInvalidValue;
+  GemmArgs g = a, r = a;
+  if (p.rows) {
+    g.M = p.rows;
+    r.M = a.M - p.rows;
+    r.A = a.A + frag_index(p.rows, 0, ka);
+    if (a.C) r.C = a.C + (size_t)p.rows * a.ldc;
+    if (a.R) r.R = a.R + (size_t)p.rows * a.ldc;
+    if (a.H) r.H = a.H + frag_index(p.rows, 0, a.ldh);
+    if (a.q) r.q = a.q + (size_t)p.rows * a.ldq;
+    if (a.meta.row_pos) {
+      r.meta.row_pos = a.meta.row_pos + p.rows;
+      r.meta.row_env = a.meta.row_env + p.rows;
+    }
+  } else {
+    g.N = p.cols;
+    r.N = a.N - p.cols;
+    r.W = a.W + frag_index(p.cols, 0, kw);
+    if (a.C) r.C = a.C + p.cols;
+    if (a.R) r.R = a.R + p.cols;
+    if (a.H) r.H = a.H + frag_index(0, p.cols / 2, a.ldh);  // a 64-column group of [gate; up] is 32 features
+    r.col0 = p.cols;
+  }
+  const hipError_t e = launch_part(g, epi, p.first, s);
+  return e != hipSuccess ? e : launch_part(r, epi, p.rest, s);
 }
 
 }  // namespace vla

@@ -11,7 +11,7 @@
 // What bounds it: the copies.  With the LDS reads and the MFMAs left out a 96 x 64 tile of K = 11008 takes 56 of its
 // 60 us; deeper rings than these change nothing, because the columns of W that are in flight at one time are those of
 // N / TN tiles only and a CU's misses are served at 30-50 GB/s (256 CUs on distinct lines: 6.2 TB/s).  So a shape is
-// worth what it fills, and gemm_shape picks by the time that each would take (below).
+// worth what it fills, and gemm_plan picks by the time that each would take (below).
 #include <algorithm>
 
 #include "common.h"
@@ -128,7 +128,7 @@ __global__ __launch_bounds__(T::NT) void gemm_tiles_kernel(GemmArgs a, int tiles
   auto unit_c0 = [&](int i) { return n0 + 64 * ((wave + i * T::NW) % T::GR); };
   auto unit_r0 = [&](int i) { return 16 * ((wave + i * T::NW) / T::GR); };
   auto unit_row = [&](int i, int j) {
-    return min(m0 + unit_r0(i) + (unit_c0(i) < 2 * a.d_model ? lane >> 2 : 8 * j + (lane >> 3)), M - 1);
+    return min(m0 + unit_r0(i) + (unit_c0(i) + a.col0 < 2 * a.d_model ? lane >> 2 : 8 * j + (lane >> 3)), M - 1);
   };
   if constexpr (EPI == kEpiQkvRope) {
 #pragma unroll
@@ -260,7 +260,7 @@ __global__ __launch_bounds__(T::NT) void gemm_tiles_kernel(GemmArgs a, int tiles
               make_uint4(pack2bf(o[0], o[1]), pack2bf(o[2], o[3]), pack2bf(o[4], o[5]), pack2bf(o[6], o[7]));
       } else {  // kEpiQkvRope: as in gemm_prefill.hip
         const int d = a.d_model, hd = a.head_dim, H = a.n_heads, half = hd / 2;
-        const int region = c0 / d, cc0 = c0 - region * d, head = cc0 / hd, blk = (cc0 % hd) / 64;
+        const int region = (c0 + a.col0) / d, cc0 = c0 + a.col0 - region * d, head = cc0 / hd, blk = (cc0 % hd) / 64;
         if (region < 2) {
           const int q8 = lane & 3, rl = r0 + (lane >> 2), row = m0 + rl, ai = 32 * blk + 8 * q8;
           const int2 pp = make_int2(pos[i][0], page[i][0]);
@@ -358,26 +358,60 @@ constexpr ShapeCost kShapes[kGemmShapes] = {
 };
 }  // namespace
 
-// The shape with the least estimated time: the CU with the most tiles decides, and two tiles that share a CU cost less
-// than twice one.  Over the measured sizes the choice is 1 % slower than the best shape of each on average (24 % at
-// worst); always 256 x 256 is 69 %.  The 256 x 256 tile does the most work per byte moved and stays the choice from
-// about two full rounds of its tiles on.  Measured with each product's own epilogue (us, 256 x 256 -> chosen): M = 277,
-// d = 4096: QKV 81 -> 52, O 68 -> 25, gate/up 85 -> 67, down 163 -> 58; M = 4720: O 175 -> 155, down 404 -> 356;
-// M = 4608, d = 1024: O 28 -> 18, down 51 -> 33; M = 1088, K = 256, N = 768: 11.6 -> 4.2.
-int gemm_shape(int M, int N, int K, int cus) {
-  int best = 0;
+// Estimated us of a product on one shape: the CU with the most tiles decides, and two tiles that share a CU cost less
+// than twice one.
+static float shape_cost(const ShapeCost& c, int M, int N, int K, int cus) {
+  const long long tiles = (long long)((M + c.tm - 1) / c.tm) * ((N + c.tn - 1) / c.tn);
+  const long long q = (tiles + cus - 1) / cus;
+  const float step = (float)(q / 2) * c.t2 + (float)(q % 2) * c.t1;
+  return c.first + c.more * (float)(q - 1) + 1e-3f * step * (float)(K / 32);
+}
+
+// The shape with the least estimated time.  Over the measured sizes the choice is 1 % slower than the best shape of each
+// on average (24 % at worst); always 256 x 256 is 69 %.  The 256 x 256 tile does the most work per byte moved and stays
+// the choice from about two full rounds of its tiles on.  Measured with each product's own epilogue (us, 256 x 256 ->
+// chosen): M = 277, d = 4096: QKV 81 -> 52, O 68 -> 25, gate/up 85 -> 67, down 163 -> 58; M = 4720: O 175 -> 155, down
+// 404 -> 356; M = 4608, d = 1024: O 28 -> 18, down 51 -> 33; M = 1088, K = 256, N = 768: 11.6 -> 4.2.
+//
+// From one full round of 256 x 256 tiles on, a product may also be cut by rows or columns: its first part the whole rounds
+// that fit (or one round less), the rest, which would be a nearly empty round, on a smaller shape after it.  The estimate,
+// with kCutUs for the second launch and the drain before it, has to be 3 % better than one shape's (without kCutUs a
+// 4608 x 5504 x 1024 gate/up was cut and took 61 us where it takes 58).  Measured, one shape -> cut (us): M = 2304,
+// d = 4096: gate/up 353 -> 315; M = 4720: O and down together 582 -> 524, QKV 399 -> 397, the four input gradients of a
+// layer 1530 -> 1380; M = 37760: O and down 3480 -> 3290.  With many rounds the emptier last one runs at a higher clock,
+// and less is gained than estimated: M = 6912 QKV 580 -> 567, gate/up 939 -> 936.
+constexpr float kCutUs = 10.f;
+GemmPlan gemm_plan(int M, int N, int K, int cus) {
+  GemmPlan best{};
   float tb = 0.f;
   for (int i = 0; i < kGemmShapes; ++i) {
-    const ShapeCost& c = kShapes[i];
-    const long long tiles = (long long)((M + c.tm - 1) / c.tm) * ((N + c.tn - 1) / c.tn);
-    const long long q = (tiles + cus - 1) / cus;
-    const float step = (float)(q / 2) * c.t2 + (float)(q % 2) * c.t1;
-    const float t = c.first + c.more * (float)(q - 1) + 1e-3f * step * (float)(K / 32);
+    const float t = shape_cost(kShapes[i], M, N, K, cus);
     if (i == 0) {
       tb = 0.95f * t;  // a smaller shape has to gain 5 %
     } else if (t < tb) {
       tb = t;
-      best = i;
+      best.first = i;
+    }
+  }
+  const ShapeCost& big = kShapes[0];
+  const int tm = (M + big.tm - 1) / big.tm, tn = (N + big.tn - 1) / big.tn;
+  const long long rounds = (long long)tm * tn / cus;
+  if (rounds < 1) return best;
+  tb = 0.97f * shape_cost(kShapes[best.first], M, N, K, cus);
+  for (long long r = rounds; r >= 1 && r >= rounds - 1; --r) {
+    const int cut_n = (int)(r * cus / tm), cut_m = (int)(r * cus / tn);  // tile columns, tile rows in r rounds
+    for (int by_rows = 0; by_rows < 2; ++by_rows) {
+      const int rows = by_rows ? cut_m * big.tm : 0, cols = by_rows ? 0 : cut_n * big.tn;
+      if (rows >= M || cols >= N || rows + cols == 0) continue;
+      const float t0 = kCutUs + (by_rows ? shape_cost(big, rows, N, K, cus) : shape_cost(big, M, cols, K, cus));
+      for (int i = 1; i < kGemmShapes; ++i) {
+        const float t = t0 + (by_rows ? shape_cost(kShapes[i], M - rows, N, K, cus)
+                                      : shape_cost(kShapes[i], M, N - cols, K, cus));
+        if (t < tb) {
+          tb = t;
+          best = GemmPlan{0, i, rows, cols};
+        }
+      }
     }
   }
   return best;

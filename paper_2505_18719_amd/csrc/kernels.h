@@ -56,13 +56,20 @@ struct GemmArgs {
   RowMeta meta;
   const float2* rope;  // [pos][head_dim / 2] (cos, sin)
   int d_model, n_heads, head_dim;
+  int col0;            // column of the packed [q; k; v] that W's row 0 is (gemm_tiles.hip: the second part of a product)
 };
 
 // Tile shapes of the prefill GEMM: 0 the 256 x 256 kernel of gemm_prefill.hip, the others gemm_tiles.hip's.  The
-// results are the same bits from each; launch_gemm runs gemm_shape's choice unless given a shape (test hook).
-hipError_t launch_gemm(const GemmArgs& a, GemmEpilogue epi, hipStream_t s, int shape = -1);
+// results are the same bits from each.
 constexpr int kGemmShapes = 9;
-int gemm_shape(int M, int N, int K, int cus);
+// How a product runs: whole on one shape, or its first `rows` rows or `cols` columns (one of them nonzero, a multiple of
+// 256 below M or N) on shape `first` and the rest on shape `rest` (> 0).
+struct GemmPlan {
+  int first, rest, rows, cols;
+};
+GemmPlan gemm_plan(int M, int N, int K, int cus);
+hipError_t launch_gemm(const GemmArgs& a, GemmEpilogue epi, hipStream_t s);  // by gemm_plan
+hipError_t launch_gemm(const GemmArgs& a, GemmEpilogue epi, hipStream_t s, const GemmPlan& plan);
 hipError_t launch_gemm_shape(const GemmArgs& a, GemmEpilogue epi, int shape, hipStream_t s);
 
 // Skinny GEMM for decode: C = A[M, K] * W[N, K]^T for M <= 128 rows, N % 64 == 0,

@@ -1,5 +1,5 @@
 """The prefill GEMM's tile shapes in the model: a batch whose GEMMs run 256 x 256 tiles and one environment of it,
-whose GEMMs run smaller tiles, give the same bits through every epilogue (residual, SwiGLU, RoPE + KV append, and the
+whose GEMMs run smaller tiles, or are cut by rows or columns into both, give the same bits through every epilogue (residual, SwiGLU, RoPE + KV append, and the
 kept pre-activations of the gradient's forward)."""
 import numpy as np
 import pytest
@@ -11,7 +11,8 @@ from paper_2505_18719_amd import inputs, vla
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("d,heads,ffn,batch", [(256, 4, 688, 40), (1024, 8, 2752, 96), (2048, 16, 5496, 64)])
+@pytest.mark.parametrize("d,heads,ffn,batch", [(256, 4, 688, 40), (1024, 8, 2752, 20), (1024, 8, 2752, 96), (2048, 16, 5496, 48),
+                                               (2048, 16, 5496, 64)])
 def test_one_environment_matches_the_batch(d, heads, ffn, batch):
     cfg = inputs.TINY.replace(name="shapes", d_model=d, n_heads=heads, d_ffn=ffn, batch=batch, prompt_min=0,
                               prompt_max=57)

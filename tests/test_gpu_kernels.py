@@ -122,3 +122,16 @@ def test_prefill_gemm_shapes_give_the_same_bits(M, N, K):
         C = vla.debug_gemm(A, W, shape=shape)
         torch.cuda.synchronize()
         assert torch.equal(C, ref), shape
+
+
+# cut by columns (9 .. 16) and by rows (17 .. 24), the rest on every smaller shape: rests of one row or one column group,
+# and beside the edges of tiles
+@pytest.mark.parametrize("M,N,K", [(257, 320, 96), (300, 256 + 192, 704), (500, 1088, 64)])
+def test_prefill_gemm_cuts_give_the_same_bits(M, N, K):
+    from paper_2505_18719_amd import vla
+    A, W = _rand_bf16((M, K), 23), _rand_bf16((N, K), 24, 0.02)
+    ref = vla.debug_gemm(A, W, shape=0)
+    for shape in range(9, 25):
+        C = vla.debug_gemm(A, W, shape=shape)
+        torch.cuda.synchronize()
+        assert torch.equal(C, ref), shape
