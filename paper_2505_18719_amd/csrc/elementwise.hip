@@ -3,7 +3,10 @@
 // GEMM's split-K partials (residual add + RMSNorm, SwiGLU, RoPE + KV append,
 // logits), and one-time weight repacking.  All loads and stores are 16-byte
 // vectors where the layout allows.
+#include <algorithm>
+
 #include "common.h"
+#include "embed_dev.h"
 #include "kernels.h"
 
 namespace vla {
@@ -124,75 +127,27 @@ __global__ __launch_bounds__(64 * RPW) void rmsnorm_frag_kernel(const float* __r
     *reinterpret_cast<uint4*>(ub + (size_t)kb * 512) = *reinterpret_cast<const uint4*>(src + 64 * kb);
 }
 
-// Block-wide sum over 256 threads.
-__device__ __forceinline__ float block_sum256(float v, float* sh) {
-  v = wave_sum(v);
-  const int w = threadIdx.x >> 6;
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) sh[w] = v;
-  __syncthreads();
-  return sh[0] + sh[1] + sh[2] + sh[3];
-}
-
-constexpr int kMaxPerThread = 32;  // d <= 8192
-
-__global__ __launch_bounds__(256) void embed_token_norm_kernel(const int32_t* tok, const bf16_t* emb, float* x,
-                                                               bf16_t* u, const float* g, float eps, int d,
-                                                               int vocab, uint32_t* flags) {
+__global__ __launch_bounds__(256) void embed_token_norm_kernel(const int32_t* tok, EmbedTokenArgs a) {
   __shared__ float sh[4];
-  const int b = blockIdx.x;
-  int id = tok[b];
-  const bool ok = id >= 0 && id < vocab;
-  if (!ok && threadIdx.x == 0) atomicOr(flags, 1u);
-  float v[kMaxPerThread];
-  float ss = 0.f;
-  const int n = (d / 4 + 255) / 256;  // groups of 4 columns per thread
-#pragma unroll
-  for (int t = 0; t < kMaxPerThread / 4; ++t) {
-    if (t >= n) break;
-    const int c = 4 * (threadIdx.x + 256 * t);
-    if (c >= d) {
-      v[4 * t] = v[4 * t + 1] = v[4 * t + 2] = v[4 * t + 3] = 0.f;
-      continue;
-    }
-    const uint2 e = ok ? *reinterpret_cast<const uint2*>(emb + (size_t)id * d + c) : make_uint2(0, 0);
-    v[4 * t] = __uint_as_float(e.x << 16);
-    v[4 * t + 1] = __uint_as_float(e.x & 0xffff0000u);
-    v[4 * t + 2] = __uint_as_float(e.y << 16);
-    v[4 * t + 3] = __uint_as_float(e.y & 0xffff0000u);
-    ss += v[4 * t] * v[4 * t] + v[4 * t + 1] * v[4 * t + 1] + v[4 * t + 2] * v[4 * t + 2] +
-          v[4 * t + 3] * v[4 * t + 3];
-  }
-  ss = block_sum256(ss, sh);
-  const float r = rsqrtf(ss / (float)d + eps);
-#pragma unroll
-  for (int t = 0; t < kMaxPerThread / 4; ++t) {
-    if (t >= n) break;
-    const int c = 4 * (threadIdx.x + 256 * t);
-    if (c >= d) break;
-    const float4 gv = *reinterpret_cast<const float4*>(g + c);
-    *reinterpret_cast<float4*>(x + (size_t)b * d + c) = make_float4(v[4 * t], v[4 * t + 1], v[4 * t + 2], v[4 * t + 3]);
-    *reinterpret_cast<uint2*>(u + frag_index(b, c, d)) =
-        make_uint2(pack2bf(v[4 * t] * r * gv.x, v[4 * t + 1] * r * gv.y),
-                   pack2bf(v[4 * t + 2] * r * gv.z, v[4 * t + 3] * r * gv.w));
-  }
+  embed_token_row(a, tok[blockIdx.x], blockIdx.x, sh);
 }
 
-
-// One 1024-thread workgroup per row: 4 consecutive columns per thread and
-// pass (two passes cover d <= 8192), every partial slot's float4 in flight together.
+// One workgroup per row: 4 consecutive columns per thread and pass (1024 threads in two passes cover d <= 8192, smaller
+// rows take d / 4 threads), the partial slots' float4s and the gain in flight together.  Two waits bound it (the loads,
+// the sum over the waves); the gain's load after them was a third.  d = 256: 2.7 -> 2.6 us, d = 1024: 3.9 -> 3.7.
 __global__ __launch_bounds__(1024) void reduce_residual_norm_kernel(const float* __restrict__ part, SkinnyPlan p,
                                                                     float* __restrict__ x, bf16_t* __restrict__ u,
                                                                     const float* __restrict__ g, float eps, int M,
                                                                     int d) {
   __shared__ float sh[16];
   const int m = blockIdx.x;
-  float4 v[2];
+  float4 v[2], gv[2];
   float ss = 0.f;
 #pragma unroll
   for (int t = 0; t < 2; ++t) {  // d <= 8192
     const int c = 4 * (threadIdx.x + 1024 * t);
     if (c >= d) break;
+    gv[t] = *reinterpret_cast<const float4*>(g + c);
     const float4 a = sum_slots4(part + (size_t)m * d + c, (size_t)M * d, skinny_slots(p, c >> 6),
                                 *reinterpret_cast<const float4*>(x + (size_t)m * d + c));
     v[t] = a;
@@ -203,25 +158,29 @@ __global__ __launch_bounds__(1024) void reduce_residual_norm_kernel(const float*
   __syncthreads();
   ss = 0.f;
 #pragma unroll
-  for (int w = 0; w < 16; ++w) ss += sh[w];
+  for (int w = 0; w < 16; ++w)
+    if (w < (int)blockDim.x / 64) ss += sh[w];
   const float r = rsqrtf(ss / (float)d + eps);
 #pragma unroll
   for (int t = 0; t < 2; ++t) {
     const int c = 4 * (threadIdx.x + 1024 * t);
     if (c >= d) break;
-    const float4 gv = *reinterpret_cast<const float4*>(g + c);
     *reinterpret_cast<float4*>(x + (size_t)m * d + c) = v[t];
     *reinterpret_cast<uint2*>(u + frag_index(m, c, d)) =
-        make_uint2(pack2bf(v[t].x * r * gv.x, v[t].y * r * gv.y), pack2bf(v[t].z * r * gv.z, v[t].w * r * gv.w));
+        make_uint2(pack2bf(v[t].x * r * gv[t].x, v[t].y * r * gv[t].y),
+                   pack2bf(v[t].z * r * gv[t].z, v[t].w * r * gv[t].w));
   }
 }
 
 __global__ __launch_bounds__(256) void reduce_sum_kernel(const float* __restrict__ part, SkinnyPlan p,
-                                                         float* __restrict__ z, int M, int N) {
+                                                         float* __restrict__ z, int M, int N,
+                                                         float* __restrict__ z2) {
   const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
   if (i >= (size_t)M * N) return;
   const int m = (int)(i / N), n = (int)(i % N);
-  z[i] = skinny_sum(part, p, M, p.tiles * 64, m, n);
+  const float v = skinny_sum(part, p, M, p.tiles * 64, m, n);
+  z[i] = v;
+  if (z2) z2[i] = v;
 }
 
 __global__ __launch_bounds__(256) void reduce_swiglu_kernel(const float* __restrict__ part, SkinnyPlan p,
@@ -349,7 +308,8 @@ hipError_t launch_embed_token_norm(const int32_t* tok, const bf16_t* emb, float*
                                    float eps, int B, int d, int vocab, uint32_t* flags, hipStream_t s) {
   if (B <= 0) return hipSuccess;
   if (d > 256 * kMaxPerThread || d % 32 != 0) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(embed_token_norm_kernel, dim3(B), dim3(256), 0, s, tok, emb, x, u, g, eps, d, vocab, flags);
+  const EmbedTokenArgs a{emb, x, u, g, eps, d, vocab, flags};
+  hipLaunchKernelGGL(embed_token_norm_kernel, dim3(B), dim3(256), 0, s, tok, a);
   return hipGetLastError();
 }
 
@@ -357,15 +317,17 @@ hipError_t launch_reduce_residual_norm(const float* part, const SkinnyPlan& p, f
                                        float eps, int M, int d, hipStream_t s) {
   if (M <= 0) return hipSuccess;
   if (d > 8192 || d % 64 != 0 || p.tiles * 64 != d) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(reduce_residual_norm_kernel, dim3(M), dim3(1024), 0, s, part, p, x, u, g, eps, M, d);
+  hipLaunchKernelGGL(reduce_residual_norm_kernel, dim3(M), dim3(std::min(1024, (d / 4 + 63) / 64 * 64)), 0, s, part, p, x, u, g, eps, M, d);
   return hipGetLastError();
 }
 
-hipError_t launch_reduce_sum(const float* part, const SkinnyPlan& p, float* z, int M, int N, hipStream_t s) {
+hipError_t launch_reduce_sum(const float* part, const SkinnyPlan& p, float* z, int M, int N, hipStream_t s,
+                             float* z2) {
   const size_t n = (size_t)M * N;
   if (n == 0) return hipSuccess;
   if (N > p.tiles * 64) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(reduce_sum_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, part, p, z, M, N);
+  hipLaunchKernelGGL(reduce_sum_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, part, p, z, M, N,
+                     z2);
   return hipGetLastError();
 }
 

@@ -101,34 +101,33 @@ __host__ __device__ inline int skinny_slots(const SkinnyPlan& p, int tile) {
   const int U = (p.tiles - p.dp_tiles) * p.chunks, t = tile - p.dp_tiles;
   return skinny_owner((t + 1) * p.chunks - 1, U, p.G) - skinny_owner(t * p.chunks, U, p.G) + 1;
 }
-// Partial slots loaded together before they are summed (more slots: summed one by one after).
+// Partial slots loaded together before they are summed.
 constexpr int kSlotsAhead = 8;
 
 // v + the sum of ns partial slots (slot s at p[s * stride]), added in slot order.
 __device__ inline float sum_slots(const float* __restrict__ p, size_t stride, int ns, float v) {
-  float q[kSlotsAhead];
+  for (int s0 = 0; s0 < ns; s0 += kSlotsAhead) {
+    float q[kSlotsAhead];
 #pragma unroll
-  for (int s = 0; s < kSlotsAhead; ++s)
-    if (s < ns) q[s] = p[s * stride];
+    for (int s = 0; s < kSlotsAhead; ++s)
+      if (s0 + s < ns) q[s] = p[(s0 + s) * stride];
 #pragma unroll
-  for (int s = 0; s < kSlotsAhead; ++s)
-    if (s < ns) v += q[s];
-  for (int s = kSlotsAhead; s < ns; ++s) v += p[s * stride];
+    for (int s = 0; s < kSlotsAhead; ++s)
+      if (s0 + s < ns) v += q[s];
+  }
   return v;
 }
 __device__ inline float4 sum_slots4(const float* __restrict__ p, size_t stride, int ns, float4 v) {
-  float4 q[kSlotsAhead];
+  for (int s0 = 0; s0 < ns; s0 += kSlotsAhead) {
+    float4 q[kSlotsAhead];
 #pragma unroll
-  for (int s = 0; s < kSlotsAhead; ++s)
-    if (s < ns) q[s] = *reinterpret_cast<const float4*>(p + s * stride);
+    for (int s = 0; s < kSlotsAhead; ++s)
+      if (s0 + s < ns) q[s] = *reinterpret_cast<const float4*>(p + (s0 + s) * stride);
 #pragma unroll
-  for (int s = 0; s < kSlotsAhead; ++s)
-    if (s < ns) {
-      v.x += q[s].x; v.y += q[s].y; v.z += q[s].z; v.w += q[s].w;
-    }
-  for (int s = kSlotsAhead; s < ns; ++s) {
-    const float4 t = *reinterpret_cast<const float4*>(p + s * stride);
-    v.x += t.x; v.y += t.y; v.z += t.z; v.w += t.w;
+    for (int s = 0; s < kSlotsAhead; ++s)
+      if (s0 + s < ns) {
+        v.x += q[s].x; v.y += q[s].y; v.z += q[s].z; v.w += q[s].w;
+      }
   }
   return v;
 }
@@ -201,7 +200,9 @@ hipError_t launch_embed_token_norm(const int32_t* tok, const bf16_t* emb, float*
 hipError_t launch_reduce_residual_norm(const float* part, const SkinnyPlan& p, float* x, bf16_t* u,
                                        const float* g, float eps, int M, int d, hipStream_t s);
 // z[m, n] = C[m, n] for n < N (z rows of N floats)
-hipError_t launch_reduce_sum(const float* part, const SkinnyPlan& p, float* z, int M, int N, hipStream_t s);
+// z2 (may be null): a second copy
+hipError_t launch_reduce_sum(const float* part, const SkinnyPlan& p, float* z, int M, int N, hipStream_t s,
+                             float* z2 = nullptr);
 // h[m, j] = bf16(silu(C[m, gate_j]) * C[m, up_j]) for j < F (h in frag layout, K = ldh),
 // C's columns interleaved
 // as [32 gate; 32 up] blocks (column 64 (j / 32) + j % 32 and 32 further)
@@ -246,9 +247,22 @@ struct DecodeAttnArgs {
 };
 hipError_t launch_attn_decode(const DecodeAttnArgs& a, hipStream_t s);
 
+// A decode step's input of row b from its token: x = emb[token], u = RMSNorm(x) g in frag layout.
+struct EmbedTokenArgs {
+  const bf16_t* emb;
+  float* x;
+  bf16_t* u;
+  const float* g;
+  float eps;
+  int d, vocab;
+  uint32_t* flags;
+};
+
 // Sampler over the action bins (one wave per row).
 struct SamplerArgs {
-  const float* z;          // [rows, A] logits
+  const float* z;          // [rows, A] logits, or null: the slots of the head's skinny GEMM over the same rows
+  const float* part;
+  SkinnyPlan plan;
   int A;
   float temperature;
   // sampling mode (gumbel != null): row b, step i
@@ -265,6 +279,8 @@ struct SamplerArgs {
   uint32_t* flags;
 };
 hipError_t launch_sampler(const SamplerArgs& a, hipStream_t s);
+// Sampling mode, and the next decode step's input: launch_embed_token_norm of the sampled tokens.
+hipError_t launch_sampler_embed(const SamplerArgs& a, const EmbedTokenArgs& e, hipStream_t s);
 
 // Weight packing (one-time, at create): dst [rows, K] in frag layout (see frag_index)
 enum PackMode { kPackRows = 0, kPackQk = 1, kPackGateUp = 2 };

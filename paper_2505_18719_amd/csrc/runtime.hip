@@ -290,13 +290,14 @@ double gemm_flops(double M, double N, double K) { return 2.0 * M * N * K; }
 double skinny_bytes(double N, double K, double M) { return 2.0 * N * K + 2.0 * M * K; }
 
 // Skinny GEMM over up to kSkinnyRows rows, followed by the logits reduction.
-int head_logits(vla_model* m, const bf16_t* u, int R, float* logits, hipStream_t s) {
+int head_logits(vla_model* m, const bf16_t* u, int R, float* logits, hipStream_t s, float* copy = nullptr) {
   const Dims& D = m->D;
   for (int r0 = 0; r0 < R; r0 += kSkinnyRows) {
     const int rows = std::min(kSkinnyRows, R - r0);
     SkinnyArgs sa{u + frag_index(r0, 0, D.d), rows, m->lm_act, D.Ap, D.d, m->part};
     VLA_CK(launch_skinny(sa, m->plan_head, s));
-    VLA_CK(launch_reduce_sum(m->part, m->plan_head, logits + (size_t)r0 * D.A, rows, D.A, s));
+    VLA_CK(launch_reduce_sum(m->part, m->plan_head, logits + (size_t)r0 * D.A, rows, D.A, s,
+                             copy ? copy + (size_t)r0 * D.A : nullptr));
   }
   return VLA_OK;
 }
@@ -902,9 +903,8 @@ int vla_prefill(vla_model* m, int32_t B, const void* vis, const int32_t* ids, co
   int R = 0;
   int rc = forward(m, B, vis, ids, lens_host, nullptr, s, &R);
   if (rc) return rc;
-  rc = head_logits(m, m->u_head, R, m->logits_pre, s);
+  rc = head_logits(m, m->u_head, R, m->logits_pre, s, logits);
   if (rc) return rc;
-  VLA_CK(hipMemcpyAsync(logits, m->logits_pre, (size_t)B * m->D.A * sizeof(float), hipMemcpyDeviceToDevice, s));
   m->prefix_host.assign(B, 0);
   for (int b = 0; b < B; ++b) m->prefix_host[b] = m->D.nvis + lens_host[b];
   m->state_batch = B;
@@ -937,8 +937,6 @@ int vla_decode_actions(vla_model* m, int32_t B, const float* gumbel, float T, in
       if (rc) return rc;
       z = m->logits_dec;
     } else if (i > 0) {
-      VLA_CK(launch_embed_token_norm(m->next_tok, m->emb, m->x, m->u, m->lw[0].attn_norm, eps, B, D.d, D.V, m->flags,
-                                     s));
       // The decode GEMMs take at most kSkinnyRows rows: larger batches run the
       // layer stack once per chunk of environments (each chunk streams the weights).
       for (int r0 = 0; r0 < B; r0 += kSkinnyRows) {
@@ -970,15 +968,26 @@ int vla_decode_actions(vla_model* m, int32_t B, const float* gumbel, float T, in
           VLA_CK(launch_reduce_residual_norm(m->part, m->plan_d, x, u, gnext, eps, rows, D.d, s));
         }
       }
-      int rc = head_logits(m, m->u, B, m->logits_dec, s);
-      if (rc) return rc;
-      z = m->logits_dec;
+      if (B <= kSkinnyRows) {  // the sampler adds the head's slots itself
+        SkinnyArgs sh{m->u, B, m->lm_act, D.Ap, D.d, m->part};
+        VLA_CK(launch_skinny(sh, m->plan_head, s));
+        z = nullptr;
+      } else {
+        int rc = head_logits(m, m->u, B, m->logits_dec, s);
+        if (rc) return rc;
+        z = m->logits_dec;
+      }
     }
     SamplerArgs sa{};
-    sa.z = z; sa.A = D.A; sa.temperature = T; sa.gumbel = gumbel; sa.step = i; sa.n_actions = D.nact;
+    sa.z = z; sa.part = m->part; sa.plan = m->plan_head; sa.A = D.A; sa.temperature = T; sa.gumbel = gumbel; sa.step = i; sa.n_actions = D.nact;
     sa.action_begin = m->cfg.action_begin; sa.tokens = tokens; sa.next_tok = m->next_tok; sa.logp = logp;
     sa.entropy = entropy; sa.logits_out = step_logits; sa.rows = B; sa.flags = m->flags;
-    VLA_CK(launch_sampler(sa, s));
+    if (!fused && i + 1 < D.nact) {
+      const EmbedTokenArgs ea{m->emb, m->x, m->u, m->lw[0].attn_norm, eps, D.d, D.V, m->flags};
+      VLA_CK(launch_sampler_embed(sa, ea, s));
+    } else {
+      VLA_CK(launch_sampler(sa, s));
+    }
   }
   g_err.clear();
   return VLA_OK;
