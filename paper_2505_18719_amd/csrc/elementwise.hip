@@ -259,6 +259,19 @@ __global__ void bf16_to_f32_kernel(float* dst, const bf16_t* src, int n) {
   if (i < n) dst[i] = bf2f(src[i]);
 }
 
+// dst = src, 4 x 16 bytes per thread; the stores bypass the caches (404 MB: 5.0 -> 5.6 TB/s, the runtime's copy
+// before).
+__global__ __launch_bounds__(256) void copy_kernel(const u32x4* __restrict__ src, u32x4* __restrict__ dst, size_t n16) {
+  const size_t i0 = (size_t)blockIdx.x * 1024 + threadIdx.x;
+  u32x4 v[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u)
+    if (i0 + 256 * u < n16) v[u] = src[i0 + 256 * u];
+#pragma unroll
+  for (int u = 0; u < 4; ++u)
+    if (i0 + 256 * u < n16) __builtin_nontemporal_store(v[u], dst + i0 + 256 * u);
+}
+
 __global__ void fill_zero_kernel(uint4* dst, size_t n16) {
   for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n16; i += (size_t)gridDim.x * 256)
     dst[i] = make_uint4(0, 0, 0, 0);
@@ -340,67 +353,56 @@ hipError_t launch_reduce_swiglu(const float* part, const SkinnyPlan& p, bf16_t* 
   return hipGetLastError();
 }
 
-// LoRA merge, one 256-thread workgroup per 64 rows x 64 K columns.  Rows are
+// LoRA merge, one 256-thread workgroup per kMergeRows rows x kMergeCols K columns.  Rows are
 // the projection's own rows in packed order: for the interleaved [gate; up]
 // weight only the 32-row halves of `part`, so no workgroup computes rows it
-// does not write.  The update B A of the tile is a 64 x 64 x rank product on
-// MFMA: wave w takes rows 16 w .. 16 w + 15, its A operand the 16 B rows of
-// their source rows (contiguous 16-byte reads), its B operand the adapter's A
-// factor staged transposed in LDS.  The original weights are loaded first;
-// each wave stages its fp32 update in its own LDS rows (no workgroup barrier
-// after the staging of A), adds two 8-element chunks per lane to the original
-// weights, rounds to bf16 and writes them in frag layout.  (Measured: wider
-// tiles that reuse the staged A over 128 or 256 columns are slower, 7.7 and
-// 12.1 ms against 6.9 ms for every projection of the 7B shape at rank 32:
-// fewer workgroups fit on a CU to cover the loads' latency.)
-constexpr int kMergeCols = 64;
+// does not write.  The update is taken transposed, A^T B^T on MFMA, a 16-row block of the projection in the columns of
+// the product and K columns 8 (i / 4) + 4 t + i % 4 of a 32-column block in row i of its tiles t = 0, 1: lane (row
+// l % 16, K elements 8 (l / 16) ..) then holds the update of the 16 bytes that it holds in frag layout, so the original
+// weights are loaded to that layout, the update is added in registers, and every store is a whole 1 KB block.  A^T of the
+// tile's columns is staged in LDS; B's rows are MFMA operands as they lie.
+// The merge is a copy with an update: tiles 128 columns wide, taken along the rows of the original weights, read 256-byte
+// pieces of rows that other workgroups are reading on, and the stores, which nothing reads soon, bypass the caches.  All
+// projections of the 7B shape at rank 32 (810 MB): 182 us (64 x 64 tiles taken down the columns, the update staged in
+// LDS) -> 170 -> 163 us with those stores = 5.0 TB/s, what a plain copy reaches; 128 x 128 tiles 166, 64 x 256 227, several
+// row steps per workgroup with the next one's loads in flight 175-190, loads that bypass the caches as well 176.
+constexpr int kMergeRows = 64, kMergeCols = 128;
 
 // Rows of the projection a merge computes (for [gate; up], the part's half of the packed rows).
 __host__ __device__ inline int merge_rows(const MergeArgs& a) { return a.mode == kPackGateUp ? a.rows / 2 : a.rows; }
 
-// Tile (rows 64 rb .., columns kMergeCols cb ..) of one merge.
+// Tile (rows kMergeRows rb .., columns kMergeCols cb ..) of one merge.
 __device__ __forceinline__ void merge_tile(const MergeArgs& a, int rb, int cb) {
+  constexpr int RB = kMergeRows / 64, CB = kMergeCols / 32;             // 16-row blocks of a wave, 32-column blocks
   __shared__ __attribute__((aligned(16))) bf16_t at[kMergeCols][72];  // A^T: [column][rank], padded rows
-  __shared__ float dws[4][16][68];                                     // per wave: the block's update of its rows
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int c0 = cb * kMergeCols;
-  const int nblk = min(kMergeCols, a.K - c0) / 64;  // K % 64 == 0
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, r16 = lane & 15, g = lane >> 4;
+  const int c0 = cb * kMergeCols, nblk = min(kMergeCols, a.K - c0) / 32;
   const int RK = (a.rank + 31) / 32 * 32;
   const bool gu = a.mode == kPackGateUp;
   const int nrows = merge_rows(a);
-  // packed row of the projection's row l
-  auto prow = [&](int l) { return gu ? 64 * (l >> 5) + 32 * a.part + (l & 31) : l; };
-  // this lane's two 8-column chunks of each block: row 16 wave + e / 8, columns 8 (e % 8), e = lane + 64 t
-  int crow[2], csrc[2];
-  bool cin[2];
+  // this lane's rows: packed row and source row (-1: a zero row), their original weights and B's rank columns 8 g ..
+  int row[RB], src[RB];
+  uint4 w0[RB][CB], bv[RB][2];
 #pragma unroll
-  for (int t = 0; t < 2; ++t) {
-    const int l = rb * 64 + 16 * wave + (lane + 64 * t) / 8;
-    cin[t] = l < nrows;
-    crow[t] = prow(l);
-    int pt;
-    csrc[t] = cin[t] ? pack_src_row(a.mode, crow[t], a.head_dim, a.src_rows, pt) : -1;
-  }
-  uint4 w0v[kMergeCols / 64][2];
+  for (int i = 0; i < RB; ++i) {
+    const int l = rb * kMergeRows + 16 * (wave + 4 * i) + r16;
+    row[i] = gu ? 64 * (l >> 5) + 32 * a.part + (l & 31) : l;
+    int part;
+    src[i] = l < nrows ? pack_src_row(a.mode, row[i], a.head_dim, a.src_rows, part) : -1;
+    if (l >= nrows) row[i] = -1;
 #pragma unroll
-  for (int cb = 0; cb < kMergeCols / 64; ++cb)
-#pragma unroll
-    for (int t = 0; t < 2; ++t) {
-      const int col = c0 + 64 * cb + 8 * ((lane + 64 * t) % 8);
-      w0v[cb][t] = make_uint4(0, 0, 0, 0);  // zero rows and columns of the packed layout
-      if (cb < nblk && csrc[t] >= 0 && col < a.src_cols)  // src_cols % 8 == 0: a chunk is wholly in or out
-        w0v[cb][t] = *reinterpret_cast<const uint4*>(a.w0 + (size_t)csrc[t] * a.src_ld + col);
+    for (int c = 0; c < CB; ++c) {
+      const int col = c0 + 32 * c + 8 * g;
+      w0[i][c] = make_uint4(0, 0, 0, 0);  // zero rows and columns of the packed layout
+      if (src[i] >= 0 && col < a.src_cols)  // src_cols % 8 == 0: a chunk is wholly in or out
+        w0[i][c] = *reinterpret_cast<const uint4*>(a.w0 + (size_t)src[i] * a.src_ld + col);
     }
-  // this lane's A-operand row (row 16 wave + lane % 16) of B, both rank halves
-  const int lb = rb * 64 + 16 * wave + (lane & 15);
-  int part;
-  const int j = lb < nrows ? pack_src_row(a.mode, prow(lb), a.head_dim, a.src_rows, part) : -1;
-  uint4 bv[2];
 #pragma unroll
-  for (int kc = 0; kc < 2; ++kc) {
-    const int k = 32 * kc + 8 * (lane >> 4);
-    bv[kc] = make_uint4(0, 0, 0, 0);
-    if (kc < RK / 32 && j >= 0 && k < a.rank) bv[kc] = *reinterpret_cast<const uint4*>(a.b + (size_t)j * a.rank + k);
+    for (int kc = 0; kc < 2; ++kc) {
+      const int k = 32 * kc + 8 * g;
+      bv[i][kc] = make_uint4(0, 0, 0, 0);
+      if (src[i] >= 0 && k < a.rank) bv[i][kc] = *reinterpret_cast<const uint4*>(a.b + (size_t)src[i] * a.rank + k);
+    }
   }
   // A^T of the tile's columns, zero past the rank and past the source columns: 8 columns of one rank row per
   // 16-byte load
@@ -413,55 +415,49 @@ __device__ __forceinline__ void merge_tile(const MergeArgs& a, int rb, int cb) {
     for (int x = 0; x < 8; ++x) at[c + x][kr] = (bf16_t)(vv[x >> 1] >> (16 * (x & 1)));
   }
   __syncthreads();
-  float(*dw)[68] = dws[wave];
 #pragma unroll
-  for (int cb = 0; cb < kMergeCols / 64; ++cb) {
-    if (cb >= nblk) break;
-    f32x4 acc[4];
+  for (int c = 0; c < CB; ++c) {
+    if (c >= nblk) break;
+    bf16x8 av[2][2];  // [t][kc]
 #pragma unroll
-    for (int jb = 0; jb < 4; ++jb) acc[jb] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int t = 0; t < 2; ++t)
 #pragma unroll
-    for (int kc = 0; kc < 2; ++kc) {
-      if (kc < RK / 32) {
-        const int k = 32 * kc + 8 * (lane >> 4);
+      for (int kc = 0; kc < 2; ++kc)
+        if (kc < RK / 32)
+          av[t][kc] = as_bf16x8(*reinterpret_cast<const uint4*>(&at[32 * c + 8 * (r16 >> 2) + 4 * t + (r16 & 3)][32 * kc + 8 * g]));
 #pragma unroll
-        for (int jb = 0; jb < 4; ++jb) {
-          const uint4 av = *reinterpret_cast<const uint4*>(&at[64 * cb + 16 * jb + (lane & 15)][k]);
-          acc[jb] = mfma16(as_bf16x8(bv[kc]), as_bf16x8(av), acc[jb]);
-        }
+    for (int i = 0; i < RB; ++i) {
+      f32x4 acc[2];
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int kc = 0; kc < 2; ++kc)
+          if (kc < RK / 32) acc[t] = mfma16(av[t][kc], as_bf16x8(bv[i][kc]), acc[t]);
       }
-    }
-    // acc[jb][r]: update of row 16 wave + 4 (lane / 16) + r, column 64 cb + 16 jb + lane % 16
-#pragma unroll
-    for (int jb = 0; jb < 4; ++jb)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) dw[4 * (lane >> 4) + r][16 * jb + (lane & 15)] = acc[jb][r];
-    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): the wave's own staging rows are written
-    // add the scaled update to the original weights, round to bf16, write in frag layout
-#pragma unroll
-    for (int t = 0; t < 2; ++t) {
-      if (!cin[t]) continue;
-      const int e = lane + 64 * t, rr = e / 8, cc = 8 * (e % 8), col = c0 + 64 * cb + cc;
+      if (row[i] < 0) continue;
+      const int col = c0 + 32 * c + 8 * g;
       float w[8];
-      unpack8(w0v[cb][t], w);
-      if (csrc[t] >= 0 && col < a.src_cols) {
+      unpack8(w0[i][c], w);
+      if (src[i] >= 0 && col < a.src_cols) {
 #pragma unroll
-        for (int x = 0; x < 8; ++x) w[x] += a.scale * dw[rr][cc + x];
+        for (int x = 0; x < 8; ++x) w[x] += a.scale * acc[x >> 2][x & 3];
       }
-      *reinterpret_cast<uint4*>(a.dst + frag_index(crow[t], col, a.K)) =
-          make_uint4(pack2bf(w[0], w[1]), pack2bf(w[2], w[3]), pack2bf(w[4], w[5]), pack2bf(w[6], w[7]));
+      const uint4 ov = make_uint4(pack2bf(w[0], w[1]), pack2bf(w[2], w[3]), pack2bf(w[4], w[5]), pack2bf(w[6], w[7]));
+      __builtin_nontemporal_store(__builtin_bit_cast(u32x4, ov),
+                                  reinterpret_cast<u32x4*>(a.dst + frag_index(row[i], col, a.K)));
     }
-    __builtin_amdgcn_s_waitcnt(0xC07F);  // this block's staging reads are done before the next block's writes
   }
 }
 
-// One workgroup per tile of each item, the items' tiles one after the other (row blocks fastest).
+// One workgroup per tile of each item, the items' tiles one after the other, along the rows of the original weights.
 __global__ __launch_bounds__(256) void lora_merge_kernel(MergeBatch b) {
   int i = 0;
   while (i + 1 < b.n && (int)blockIdx.x >= b.wg0[i + 1]) ++i;
   const MergeArgs& a = b.item[i];
-  const int local = (int)blockIdx.x - b.wg0[i], nrb = (merge_rows(a) + 63) / 64;
-  merge_tile(a, local % nrb, local / nrb);
+  const int local = (int)blockIdx.x - b.wg0[i];
+  const int ncb = (a.K + kMergeCols - 1) / kMergeCols;
+  merge_tile(a, local / ncb, local % ncb);
 }
 
 static bool merge_ok(const MergeArgs& a) {
@@ -475,7 +471,7 @@ hipError_t launch_lora_merge_batch(MergeBatch b, hipStream_t s) {
   for (int i = 0; i < b.n; ++i) {
     if (b.item[i].rows < 0 || !merge_ok(b.item[i])) return hipErrorInvalidValue;
     b.wg0[i] = wg;
-    wg += (merge_rows(b.item[i]) + 63) / 64 * ((b.item[i].K + kMergeCols - 1) / kMergeCols);
+    wg += (merge_rows(b.item[i]) + kMergeRows - 1) / kMergeRows * ((b.item[i].K + kMergeCols - 1) / kMergeCols);
   }
   b.wg0[b.n] = wg;
   if (wg == 0) return hipSuccess;
@@ -544,6 +540,15 @@ hipError_t launch_gather_rows(const float* x, const bf16_t* o, const int32_t* ro
   if (R <= 0) return hipSuccess;
   if (d % 8 != 0) return hipErrorInvalidValue;
   hipLaunchKernelGGL(gather_rows_kernel, dim3(R), dim3(256), 0, s, x, o, rows, d, xc, oc);
+  return hipGetLastError();
+}
+
+hipError_t launch_copy(void* dst, const void* src, size_t bytes, hipStream_t s) {
+  if (bytes == 0) return hipSuccess;
+  if (((uintptr_t)dst | (uintptr_t)src | bytes) % 16 != 0) return hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToDevice, s);
+  const size_t n16 = bytes / 16;
+  hipLaunchKernelGGL(copy_kernel, dim3((unsigned)((n16 + 1023) / 1024)), dim3(256), 0, s, static_cast<const u32x4*>(src),
+                     static_cast<u32x4*>(dst), n16);
   return hipGetLastError();
 }
 

@@ -1362,7 +1362,7 @@ int vla_debug_read(vla_model* m, int32_t which, int32_t layer, void* dst, size_t
     default: return fail(VLA_EINVAL, "unknown buffer");
   }
   if (bytes > avail) return fail(VLA_EINVAL, "read larger than the buffer");
-  VLA_CK(hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToDevice, static_cast<hipStream_t>(stream)));
+  VLA_CK(launch_copy(dst, src, bytes, static_cast<hipStream_t>(stream)));
   return VLA_OK;
 }
 
