@@ -433,13 +433,14 @@ int forward(vla_model* m, int B, const void* vis, const int32_t* prompt_ids, con
   // causal attention flops of one layer: q.k and p.v over (t + 1) keys per row
   double attn_flops = 0.0;
   for (int b = 0; b < B; ++b) attn_flops += 2.0 * D.d * (double)rows[b] * (rows[b] + 1);
-  EmbedArgs ea{m->x, m->emb, static_cast<const bf16_t*>(vis), prompt_ids, actions, m->row_pos, m->row_env,
+  float* const x0 = sv ? sv->xs[0] : m->x;  // the first layer's input
+  EmbedArgs ea{x0, m->emb, static_cast<const bf16_t*>(vis), prompt_ids, actions, m->row_pos, m->row_env,
                m->env_prefix, m->env_prompt_off, Mi, D.d, D.nvis, D.nact, D.V, m->flags};
   VLA_CK(launch_embed(ea, s));
   const float eps = m->cfg.rms_eps;
   // the prefill GEMMs read their activations (u, attention output, h) in frag layout
   const bool full = sv && sv->full;
-  VLA_CK(launch_rmsnorm(m->x, D.d, nullptr, m->lw[0].attn_norm, eps, full ? sv->u1[0] : m->u, D.d, Mi, D.d, s, true));
+  VLA_CK(launch_rmsnorm(x0, D.d, nullptr, m->lw[0].attn_norm, eps, full ? sv->u1[0] : m->u, D.d, Mi, D.d, s, true));
   const int n_layers = m->layer_limit > 0 ? std::min(m->layer_limit, D.L) : D.L;
   // Only the rows read afterwards (head_rows: the last prefix row, or the n_actions
   // scoring rows, of each environment) need the last layer's output; its other rows
@@ -457,10 +458,8 @@ int forward(vla_model* m, int B, const void* vis, const int32_t* prompt_ids, con
     // debug stop points inside the last layer of a limited pass (every buffer read afterwards holds that stage)
     const int stop = m->layer_limit > 0 && l == n_layers - 1 ? m->debug_stop : 0;
     if (stop == 1) break;  // u: the attention norm's output, x: the layer input
-    // keep mode chains the residual stream through the kept buffers (x_l -> xm_l -> x_{l+1}, the
+    // training chains the residual stream through the kept buffers (x_l -> the mid residual -> x_{l+1}, the
     // residual epilogues reading one and writing the next); otherwise it is updated in place
-    if (sv && !(full && l > 0))
-      VLA_CK(hipMemcpyAsync(sv->xs[l], m->x, (size_t)Mi * D.d * sizeof(float), hipMemcpyDeviceToDevice, s));
     bf16_t* const qb = full ? sv->q[l] : m->q;
     GemmArgs g{};
     g.A = full ? sv->u1[l] : m->u; g.W = w.wqkv; g.M = Mi; g.N = 3 * D.d; g.K = D.d;
@@ -484,9 +483,9 @@ int forward(vla_model* m, int B, const void* vis, const int32_t* prompt_ids, con
     }
     GemmArgs go{};
     go.A = u; go.W = w.wo; go.M = Ml; go.N = D.d; go.K = D.d; go.C = x; go.ldc = D.d;
-    if (full) {
+    if (sv) {
       go.R = sv->xs[l];
-      go.C = x = sv->xm[l];
+      go.C = x = full ? sv->xm[l] : m->x;
     }
     PROF_LAUNCH(VLA_PROF_PREFILL_GEMM, gemm_flops(Ml, D.d, D.d), launch_gemm(go, kEpiResidual, s));
     if (full) u = sv->u2[l];
@@ -505,8 +504,8 @@ int forward(vla_model* m, int B, const void* vis, const int32_t* prompt_ids, con
     GemmArgs gd{};
     gd.A = hbuf; gd.W = w.wd; gd.M = Ml; gd.N = D.d; gd.K = 32 * ((D.F + 31) / 32); gd.ka = D.Fp; gd.kw = D.Fp;
     gd.C = x; gd.ldc = D.d;
-    if (full) {
-      gd.R = sv->xm[l];
+    if (sv) {
+      gd.R = x;
       gd.C = x = l + 1 < D.L ? sv->xs[l + 1] : m->x;
     }
     PROF_LAUNCH(VLA_PROF_PREFILL_GEMM, gemm_flops(Ml, D.d, D.F), launch_gemm(gd, kEpiResidual, s));
@@ -637,9 +636,8 @@ int layer_backward(vla_model* m, TrainBufs& t, int l, int B, int M, const vla_lo
     PrefillAttnArgs pa{qb, ob, m->kv[l], m->page_table, D.max_pages, m->env_row0, m->env_len,
                        B, d, D.H, D.hd, m->scale, nullptr, stats};
     PROF_LAUNCH(VLA_PROF_PREFILL_ATTN, 0.0, launch_attn_prefill(pa, s));
-    VLA_CK(hipMemcpyAsync(xm, xs, (size_t)M * d * sizeof(float), hipMemcpyDeviceToDevice, s));
     GemmArgs go{};
-    go.A = ob; go.W = w.wo; go.M = M; go.N = d; go.K = d; go.C = xm; go.ldc = d;
+    go.A = ob; go.W = w.wo; go.M = M; go.N = d; go.K = d; go.R = xs; go.C = xm; go.ldc = d;
     PROF_LAUNCH(VLA_PROF_PREFILL_GEMM, gemm_flops(M, d, d), launch_gemm(go, kEpiResidual, s));
     VLA_CK(launch_rmsnorm(xm, d, nullptr, w.mlp_norm, eps, u2, d, M, d, s, true));
     PROF_LAUNCH(VLA_PROF_PREFILL_GEMM, gemm_flops(M, 2.0 * D.F, d), gemm_f32(u2, 0, w.wgu, 0, M, Fg, d, cgu, 2 * Fp, s));
