@@ -2,6 +2,8 @@
 // decoder, Sec. 3.3 "Learning Phase"): layout conversions for the backward
 // GEMMs, RMSNorm and SwiGLU backward, and the causal attention backward with
 // the inverse rotary embedding.
+#include <algorithm>
+
 #include "common.h"
 #include "kernels.h"
 
@@ -550,37 +552,69 @@ __device__ __forceinline__ int grad_row(const LoraGradArgs& a, int o) {
   return (j >= 0 && (a.mode != kPackGateUp || part == a.part)) ? j : -1;
 }
 
-// B^T of one projection as a skinny-GEMM operand: dst (bf16 frag [rows, K]) row c,
-// column o0 + o = B[grad_row(o), c] for o < n_cols and c < r, zero elsewhere.
-__global__ void pack_bt_kernel(LoraGradArgs a, int K, int rows, bf16_t* __restrict__ dst) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i >= rows * (K / 8)) return;
-  const int c = i / (K / 8), k0 = (i % (K / 8)) * 8;
+// The group's packed operands, one launch: blockIdx.y = 2 i + 0 for A of projection i, + 1 for its B^T.
+__global__ __launch_bounds__(256) void lora_pack_kernel(LoraGroup g, int kx, bf16_t* __restrict__ apk, int ky,
+                                                        bf16_t* __restrict__ bpt) {
+  const LoraGradArgs& a = g.p[blockIdx.y >> 1];
+  const bool is_b = blockIdx.y & 1;
+  const int K = is_b ? ky : kx, t = blockIdx.x * 256 + threadIdx.x;
+  if (t >= g.r16 * (K / 8)) return;
+  const int c = t / (K / 8), k0 = (t % (K / 8)) * 8;
   float v[8];
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
-    const int o = k0 + e - a.o0;
-    const int nr = (c < a.r && o >= 0 && o < a.n_cols) ? grad_row(a, o) : -1;
-    v[e] = nr >= 0 ? bf2f(a.b[(size_t)nr * a.r + c]) : 0.f;
+    if (is_b) {
+      const int o = k0 + e - a.o0;
+      const int nr = (c < a.r && o >= 0 && o < a.n_cols) ? grad_row(a, o) : -1;
+      v[e] = nr >= 0 ? bf2f(a.b[(size_t)nr * a.r + c]) : 0.f;
+    } else {
+      v[e] = c < a.r && k0 + e < a.in ? bf2f(a.a[(size_t)c * a.in + k0 + e]) : 0.f;
+    }
   }
   uint4 q;
   q.x = pack2bf(v[0], v[1]); q.y = pack2bf(v[2], v[3]); q.z = pack2bf(v[4], v[5]); q.w = pack2bf(v[6], v[7]);
-  *reinterpret_cast<uint4*>(dst + frag_index(c, k0, K)) = q;
+  *reinterpret_cast<uint4*>((is_b ? bpt : apk) + frag_index((blockIdx.y >> 1) * g.r16 + c, k0, K)) = q;
 }
 
-// scale and place a [64, ldc] product: dB[grad_row(o), c] = s C[c, o] (o < n_cols), or
-// dA[c, i] = s C[c, i] (i < in)
-__global__ void lora_finalize_kernel(LoraGradArgs a, const float* __restrict__ C, int ldc, bool to_b) {
-  const int e = blockIdx.x * 256 + threadIdx.x;
-  const int n = to_b ? a.n_cols : a.in;
-  if (e >= a.r * n) return;
-  const int c = e / n, o = e % n;
-  const float v = a.scale * C[(size_t)c * ldc + o];
-  if (to_b) {
-    const int nr = grad_row(a, o);
-    if (nr >= 0) a.db[(size_t)nr * a.r + c] = v;
-  } else {
-    a.da[(size_t)c * a.in + o] = v;
+// Slots summed and packed, 8 columns per thread (columns of one 64-column tile).
+__global__ __launch_bounds__(256) void reduce_frag_kernel(const float* __restrict__ part, SkinnyPlan p, int rows, int M,
+                                                          int Mk, bf16_t* __restrict__ dst) {
+  const int t = blockIdx.x * 256 + threadIdx.x, kc = Mk / 8, N = p.tiles * 64;
+  if (t >= ((rows + 15) & ~15) * kc) return;
+  const int r = t / kc, k = (t % kc) * 8;
+  float v[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  if (r < rows && k < M) {
+    const int ns = skinny_slots(p, k >> 6);
+    const float* pr = part + (size_t)r * N + k;
+    const float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
+    const float4 v0 = sum_slots4(pr, (size_t)rows * N, ns, z), v1 = sum_slots4(pr + 4, (size_t)rows * N, ns, z);
+    const float w[8] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = k + e < M ? w[e] : 0.f;
+  }
+  *reinterpret_cast<uint4*>(dst + frag_index(r, k, Mk)) =
+      make_uint4(pack2bf(v[0], v[1]), pack2bf(v[2], v[3]), pack2bf(v[4], v[5]), pack2bf(v[6], v[7]));
+}
+
+// Slots summed, scaled and placed: blockIdx.z the projection, blockIdx.y four of its rank rows, a thread one column.
+__global__ __launch_bounds__(256) void lora_finalize_kernel(LoraGroup g, const float* __restrict__ part, SkinnyPlan p,
+                                                            bool to_b, int col0) {
+  const LoraGradArgs& a = g.p[blockIdx.z];
+  const int o = blockIdx.x * 256 + threadIdx.x, c0 = 4 * blockIdx.y;
+  if (o >= (to_b ? a.n_cols : a.in)) return;
+  const int nr = to_b ? grad_row(a, o) : 0;
+  if (nr < 0) return;
+  const int N = p.tiles * 64, col = to_b ? a.o0 + o - col0 : o, rows = g.n * g.r16, ns = skinny_slots(p, col >> 6);
+  const float* pr = part + (size_t)(blockIdx.z * g.r16 + c0) * N + col;
+  float v[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u)
+    if (c0 + u < a.r) v[u] = a.scale * sum_slots(pr + (size_t)u * N, (size_t)rows * N, ns, 0.f);
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    if (c0 + u >= a.r) break;
+    if (to_b) a.db[(size_t)nr * a.r + c0 + u] = v[u];
+    else a.da[(size_t)(c0 + u) * a.in + o] = v[u];
   }
 }
 
@@ -597,16 +631,38 @@ __global__ void move_rows_kernel(const float* __restrict__ src, const int32_t* _
 
 }  // namespace
 
-hipError_t launch_pack_bt(const LoraGradArgs& a, int K, int rows, bf16_t* dst, hipStream_t s) {
-  if (K % 32 != 0 || a.r < 1 || a.r > 64 || rows % 16 != 0 || rows < a.r || rows > 128) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(pack_bt_kernel, dim3((rows * (K / 8) + 255) / 256), dim3(256), 0, s, a, K, rows, dst);
+static bool group_ok(const LoraGroup& g) {
+  if (g.n < 1 || g.n > 3 || g.r16 % 16 != 0 || g.r16 < 16 || g.n * g.r16 > 128) return false;
+  for (int i = 0; i < g.n; ++i)
+    if (g.p[i].r < 1 || g.p[i].r > g.r16) return false;
+  return true;
+}
+
+hipError_t launch_lora_pack(const LoraGroup& g, int kx, bf16_t* apk, int ky, bf16_t* bpt, hipStream_t s) {
+  if (!group_ok(g) || kx % 32 != 0 || ky % 32 != 0) return hipErrorInvalidValue;
+  const int n = g.r16 * (std::max(kx, ky) / 8);
+  hipLaunchKernelGGL(lora_pack_kernel, dim3((n + 255) / 256, 2 * g.n), dim3(256), 0, s, g, kx, apk, ky, bpt);
   return hipGetLastError();
 }
 
-hipError_t launch_lora_finalize(const LoraGradArgs& a, const float* C, int ldc, bool to_b, hipStream_t s) {
-  const int n = to_b ? a.n_cols : a.in;
-  if (a.r < 1 || a.r > 64 || n <= 0 || n > ldc) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(lora_finalize_kernel, dim3((a.r * n + 255) / 256), dim3(256), 0, s, a, C, ldc, to_b);
+hipError_t launch_reduce_frag(const float* part, const SkinnyPlan& p, int rows, int M, int Mk, bf16_t* dst, hipStream_t s) {
+  if (rows < 1 || M < 1 || Mk % 32 != 0 || M > Mk || M > p.tiles * 64) return hipErrorInvalidValue;
+  const int n = ((rows + 15) & ~15) * (Mk / 8);
+  hipLaunchKernelGGL(reduce_frag_kernel, dim3((n + 255) / 256), dim3(256), 0, s, part, p, rows, M, Mk, dst);
+  return hipGetLastError();
+}
+
+hipError_t launch_lora_finalize(const LoraGroup& g, const float* part, const SkinnyPlan& p, bool to_b, int col0, hipStream_t s) {
+  if (!group_ok(g)) return hipErrorInvalidValue;
+  int n = 0, r = 0;
+  for (int i = 0; i < g.n; ++i) {
+    const LoraGradArgs& a = g.p[i];
+    const int cols = to_b ? a.n_cols : a.in, at = to_b ? a.o0 - col0 : 0;
+    if (cols < 1 || at < 0 || at + cols > p.tiles * 64) return hipErrorInvalidValue;
+    n = std::max(n, cols);
+    r = std::max(r, a.r);
+  }
+  hipLaunchKernelGGL(lora_finalize_kernel, dim3((n + 255) / 256, (r + 3) / 4, g.n), dim3(256), 0, s, g, part, p, to_b, col0);
   return hipGetLastError();
 }
 

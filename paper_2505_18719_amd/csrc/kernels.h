@@ -429,12 +429,20 @@ struct LoraGradArgs {
   float* da;         // [r, in] fp32 out
   float* db;         // [out, r] fp32 out
 };
-// B^T as a bf16 frag [rows, K] operand: row c, column o0 + o = B[natural row of packed
-// output o, c] for o < n_cols, c < r; zero elsewhere (K % 32 == 0, rows % 16 == 0, r <= rows <= 128)
-hipError_t launch_pack_bt(const LoraGradArgs& a, int K, int rows, bf16_t* dst, hipStream_t s);
-// dB[natural row of o, c] = s C[c, o] for o < n_cols (to_b), or dA[c, i] = s C[c, i] for i < in;
-// C fp32 [64, ldc] row-major
-hipError_t launch_lora_finalize(const LoraGradArgs& a, const float* C, int ldc, bool to_b, hipStream_t s);
+// The projections of one group (they share X and dY), their factors stacked r16 rows apart (n * r16 <= 128).
+struct LoraGroup {
+  int n, r16;
+  LoraGradArgs p[3];
+};
+// The group's operands: A as bf16 frag [n r16, kx] (rows past the rank and columns past `in` zero), and B^T as bf16 frag
+// [n r16, ky]: row c, column o0 + o = B[natural row of packed output o, c] for o < n_cols, c < r; zero elsewhere.
+hipError_t launch_lora_pack(const LoraGroup& g, int kx, bf16_t* apk, int ky, bf16_t* bpt, hipStream_t s);
+// The slots of a skinny GEMM [rows, N], summed, as bf16 frag [rows, Mk]: columns past M and rows of the last 16-row block
+// past `rows` zero.
+hipError_t launch_reduce_frag(const float* part, const SkinnyPlan& p, int rows, int M, int Mk, bf16_t* dst, hipStream_t s);
+// From the slots of a skinny GEMM over the group's stacked rows, with s = scale: dB[natural row of o, c] = s C[row c, o0 +
+// o - col0] for o < n_cols (to_b), or dA[c, i] = s C[row c, i] for i < in.
+hipError_t launch_lora_finalize(const LoraGroup& g, const float* part, const SkinnyPlan& p, bool to_b, int col0, hipStream_t s);
 // fp32 rows of d: dst[rows[i]] = src[i] (scatter) or dst[i] = src[rows[i]] (gather), i < R
 hipError_t launch_move_rows(const float* src, const int32_t* rows, int R, int d, float* dst, bool scatter,
                             hipStream_t s);

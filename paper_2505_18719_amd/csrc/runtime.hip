@@ -527,7 +527,7 @@ int forward(vla_model* m, int B, const void* vis, const int32_t* prompt_ids, con
 struct TrainBufs {
   SavedActs sv;  // what the forward keeps per layer
   float *dx, *dxm, *du, *dob, *xm, *cgu, *dh, *stats, *dz, *du_h, *xc, *dxc, *logp, *dlogp;
-  float *t1, *t2, *cres, *spart;  // low-rank products and skinny-GEMM partials
+  float* spart;  // skinny-GEMM partials
   bf16_t *dxf, *dxmf, *u1, *ob, *u2, *hb, *dgu, *dqkv, *wt, *xt, *dyt, *dzf, *wact_t, *apk, *bpt, *t1f, *t2f, *do16;
 };
 
@@ -575,11 +575,8 @@ void plan_train(Layout& L, const Dims& D, TrainBufs& t, bool keep) {
   t.dxc = L.take<float>(Rh * d);
   t.logp = L.take<float>(Rh);
   t.dlogp = L.take<float>(Rh);
-  const size_t ncol = std::max(std::max(Mx64, (size_t)Fg), std::max(d, (size_t)F64));
+  const size_t ncol = std::max(std::max(Mx64, (size_t)Fg), std::max(3 * d, (size_t)F64));
   // the low-rank products of up to 128 stacked factor rows (the skinny GEMM's A operand)
-  t.t1 = L.take<float>(128 * Mx64);
-  t.t2 = L.take<float>(128 * Mx64);
-  t.cres = L.take<float>(128 * ncol);
   t.spart = L.take<float>((size_t)kMaxSplits * 128 * ncol);
   t.dxf = L.take<bf16_t>(frag_elems(Mx64, d));
   t.dxmf = L.take<bf16_t>(frag_elems(Mx64, d));
@@ -608,7 +605,7 @@ hipError_t gemm_f32(const bf16_t* A, int ka, const bf16_t* W, int kw, int M, int
   return launch_gemm(g, kEpiStoreF32, s);
 }
 
-// Backward of decoder layer l: t.dx holds dL/d(layer output) [M, d] and receives
+// Backward of decoder layer l: t.dx (fp32) and t.dxf (bf16 frag) hold dL/d(layer output) [M, d] and receive
 // dL/d(layer input) (not for layer 0, whose input is the embeddings); LoRA gradients
 // of the adapted projections are written.
 int layer_backward(vla_model* m, TrainBufs& t, int l, int B, int M, const vla_lora* lora, hipStream_t s) {
@@ -643,7 +640,6 @@ int layer_backward(vla_model* m, TrainBufs& t, int l, int B, int M, const vla_lo
     PROF_LAUNCH(VLA_PROF_PREFILL_GEMM, gemm_flops(M, 2.0 * D.F, d), gemm_f32(u2, 0, w.wgu, 0, M, Fg, d, cgu, 2 * Fp, s));
   }
   // MLP: dh = dy Wd, SwiGLU backward, du2 = d[g; up] Wgu, RMSNorm backward
-  VLA_CK(launch_to_frag(t.dx, d, M, d, d, t.dxf, s));
   VLA_CK(launch_transpose_frag(w.wd, false, Fp, d, Fp, d, t.wt, s));
   VLA_CK(gemm_f32(t.dxf, 0, t.wt, 0, M, F64, d, t.dh, Fp, s));
   VLA_CK(launch_swiglu_bwd(cgu, 2 * Fp, t.dh, Fp, M, D.F, Fp, t.dgu, t.hb, s));
@@ -668,52 +664,50 @@ int layer_backward(vla_model* m, TrainBufs& t, int l, int B, int M, const vla_lo
   // factors, 16-row aligned, into one operand, so X, dY and X^T stream once per
   // group for T1, T2 and dA.
   auto adapted = [&](int p) { return lora->a[l * 7 + p] != nullptr; };
-  auto skinny_to = [&](const bf16_t* a_op, int rows, const bf16_t* w_op, int N, int K, float* out) {
-    const SkinnyPlan sp = skinny_plan(N, K, m->cus, kMaxSplits);
-    SkinnyArgs sa{a_op, rows, w_op, N, K, t.spart};
-    hipError_t e = launch_skinny(sa, sp, s);
-    return e != hipSuccess ? e : launch_reduce_sum(t.spart, sp, out, rows, N, s);
+  SkinnyPlan sp{};  // of the last skinny GEMM, whose slots are in t.spart
+  auto skinny_to = [&](const bf16_t* a_op, int rows, const bf16_t* w_op, int N, int K) {
+    sp = skinny_plan(N, K, m->cus, kMaxSplits);
+    return launch_skinny(SkinnyArgs{a_op, rows, w_op, N, K, t.spart}, sp, s);
   };
   const int r16 = round_up(lora->rank, 16), per = 128 / r16;
-  // one projection of a group: its packed output columns o0 .. o0 + n_cols of dY (the order
-  // of `mode`), and dYT, the transposed dY rows of those columns
+  // one projection of a group: its packed output columns o0 .. o0 + n_cols of dY (the order of `mode`)
   struct Proj {
     int p, o0, n_cols, out, mode, part;
-    const bf16_t* dYT;
   };
-  // X frag [M, kx] (in real input features) with X^T rows in64 (XT); dY frag [M, ky]
-  auto group = [&](const Proj* ps, int n, const bf16_t* X, int kx, int in, const bf16_t* XT, const bf16_t* dY,
-                   int ky) -> hipError_t {
+  // X frag [M, kx] (in real input features) with X^T rows in64 (XT); dY frag [M, ky] with dY^T rows (dYT).  The factors of
+  // up to 128 stacked rows run together; each product's slots go straight into what reads them.
+  auto group = [&](const Proj* ps, int n, const bf16_t* X, int kx, int in, const bf16_t* XT, const bf16_t* dY, int ky,
+                   const bf16_t* dYT) -> hipError_t {
     hipError_t e;
-    const int in64 = round_up(in, 64);
     for (int b0 = 0; b0 < n; b0 += per) {
-      const int nb = std::min(per, n - b0), rows = nb * r16;
-      LoraGradArgs la[3];
-      for (int i = 0; i < nb; ++i) {
+      LoraGroup lg{std::min(per, n - b0), r16, {}};
+      const int rows = lg.n * r16;
+      int col0 = ps[b0].o0, col1 = 0;  // the columns of dY that these projections use
+      for (int i = 0; i < lg.n; ++i) {
         const Proj& q = ps[b0 + i];
-        la[i] = LoraGradArgs{q.o0, q.n_cols, in, q.out, q.mode, D.hd, q.part,
-                             static_cast<const bf16_t*>(lora->a[l * 7 + q.p]),
-                             static_cast<const bf16_t*>(lora->b[l * 7 + q.p]), lora->rank, lora->scale,
-                             lora->grad_a[l * 7 + q.p], lora->grad_b[l * 7 + q.p]};
-        PackArgs pa{t.apk + frag_index(i * r16, 0, kx), r16, kx, la[i].a, nullptr, in, lora->rank, in, kPackRows, D.hd};
-        if ((e = launch_pack_frag(pa, s)) != hipSuccess) return e;
-        if ((e = launch_pack_bt(la[i], ky, r16, t.bpt + frag_index(i * r16, 0, ky), s)) != hipSuccess) return e;
+        lg.p[i] = LoraGradArgs{q.o0, q.n_cols, in, q.out, q.mode, D.hd, q.part,
+                               static_cast<const bf16_t*>(lora->a[l * 7 + q.p]),
+                               static_cast<const bf16_t*>(lora->b[l * 7 + q.p]), lora->rank, lora->scale,
+                               lora->grad_a[l * 7 + q.p], lora->grad_b[l * 7 + q.p]};
+        col0 = std::min(col0, q.o0);
+        col1 = std::max(col1, q.o0 + q.n_cols);
       }
-      if ((e = skinny_to(t.apk, rows, X, Mp, kx, t.t1)) != hipSuccess) return e;
-      if ((e = launch_to_frag(t.t1, Mp, rows, M, Mk, t.t1f, s)) != hipSuccess) return e;
-      if ((e = skinny_to(t.bpt, rows, dY, Mp, ky, t.t2)) != hipSuccess) return e;
-      if ((e = launch_to_frag(t.t2, Mp, rows, M, Mk, t.t2f, s)) != hipSuccess) return e;
-      for (int i = 0; i < nb; ++i) {
-        const Proj& q = ps[b0 + i];
-        LoraGradArgs lb = la[i];
-        lb.o0 = 0;  // q.dYT holds only this projection's rows
-        if ((e = skinny_to(t.t1f + frag_index(i * r16, 0, Mk), r16, q.dYT, q.n_cols, Mk, t.cres)) != hipSuccess)
+      if ((e = launch_lora_pack(lg, kx, t.apk, ky, t.bpt, s)) != hipSuccess) return e;
+      if ((e = skinny_to(t.apk, rows, X, Mp, kx)) != hipSuccess) return e;
+      if ((e = launch_reduce_frag(t.spart, sp, rows, M, Mk, t.t1f, s)) != hipSuccess) return e;
+      if ((e = skinny_to(t.bpt, rows, dY, Mp, ky)) != hipSuccess) return e;
+      if ((e = launch_reduce_frag(t.spart, sp, rows, M, Mk, t.t2f, s)) != hipSuccess) return e;
+      // dB of all projections from one pass over their columns of dY^T, where the skinny GEMM's offsets reach
+      const bool whole = (long long)frag_elems(col1 - col0, Mk) * 2 < (1ll << 31);
+      for (int i = 0; i < (whole ? 1 : lg.n); ++i) {
+        const LoraGroup q = whole ? lg : LoraGroup{1, r16, {lg.p[i]}};
+        const int c0 = whole ? col0 : q.p[0].o0, c1 = whole ? col1 : c0 + q.p[0].n_cols;
+        if ((e = skinny_to(t.t1f + frag_index(i * r16, 0, Mk), q.n * r16, dYT + frag_index(c0, 0, Mk), c1 - c0, Mk)) != hipSuccess)
           return e;
-        if ((e = launch_lora_finalize(lb, t.cres, q.n_cols, true, s)) != hipSuccess) return e;
+        if ((e = launch_lora_finalize(q, t.spart, sp, true, c0, s)) != hipSuccess) return e;
       }
-      if ((e = skinny_to(t.t2f, rows, XT, in64, Mk, t.cres)) != hipSuccess) return e;
-      for (int i = 0; i < nb; ++i)
-        if ((e = launch_lora_finalize(la[i], t.cres + (size_t)i * r16 * in64, in64, false, s)) != hipSuccess) return e;
+      if ((e = skinny_to(t.t2f, rows, XT, round_up(in, 64), Mk)) != hipSuccess) return e;
+      if ((e = launch_lora_finalize(lg, t.spart, sp, false, 0, s)) != hipSuccess) return e;
     }
     return hipSuccess;
   };
@@ -721,34 +715,34 @@ int layer_backward(vla_model* m, TrainBufs& t, int l, int B, int M, const vla_lo
   int n = 0;
   for (int p = VLA_PROJ_Q; p <= VLA_PROJ_V; ++p)
     if (adapted(p))
-      ps[n++] = Proj{p, p * d, d, d, p == VLA_PROJ_V ? kPackRows : kPackQk, 0, t.dyt + frag_index(p * d, 0, Mk)};
+      ps[n++] = Proj{p, p * d, d, d, p == VLA_PROJ_V ? kPackRows : kPackQk, 0};
   if (n) {
     VLA_CK(launch_transpose_frag(u1, false, d, M, d, Mk, t.xt, s));
     VLA_CK(launch_transpose_frag(t.dqkv, false, 3 * d, M, 3 * d, Mk, t.dyt, s));
-    VLA_CK(group(ps, n, u1, d, d, t.xt, t.dqkv, 3 * d));
+    VLA_CK(group(ps, n, u1, d, d, t.xt, t.dqkv, 3 * d, t.dyt));
   }
   if (adapted(VLA_PROJ_O)) {
     VLA_CK(launch_transpose_frag(ob, false, d, M, d, Mk, t.xt, s));
     VLA_CK(launch_transpose_frag(t.dxmf, false, d, M, d, Mk, t.dyt, s));
-    ps[0] = Proj{VLA_PROJ_O, 0, d, d, kPackRows, 0, t.dyt};
-    VLA_CK(group(ps, 1, ob, d, d, t.xt, t.dxmf, d));
+    ps[0] = Proj{VLA_PROJ_O, 0, d, d, kPackRows, 0};
+    VLA_CK(group(ps, 1, ob, d, d, t.xt, t.dxmf, d, t.dyt));
   }
   n = 0;
   for (int p = VLA_PROJ_GATE; p <= VLA_PROJ_UP; ++p)
-    if (adapted(p)) ps[n++] = Proj{p, 0, Fg, D.F, kPackGateUp, p - VLA_PROJ_GATE, t.dyt};
+    if (adapted(p)) ps[n++] = Proj{p, 0, Fg, D.F, kPackGateUp, p - VLA_PROJ_GATE};
   if (n) {
     VLA_CK(launch_transpose_frag(u2, false, d, M, d, Mk, t.xt, s));
     VLA_CK(launch_transpose_frag(t.dgu, false, 2 * Fp, M, Fg, Mk, t.dyt, s));
-    VLA_CK(group(ps, n, u2, d, d, t.xt, t.dgu, 2 * Fp));
+    VLA_CK(group(ps, n, u2, d, d, t.xt, t.dgu, 2 * Fp, t.dyt));
   }
   if (adapted(VLA_PROJ_DOWN)) {
     VLA_CK(launch_transpose_frag(t.hb, false, Fp, M, D.F, Mk, t.xt, s));
     VLA_CK(launch_transpose_frag(t.dxf, false, d, M, d, Mk, t.dyt, s));
-    ps[0] = Proj{VLA_PROJ_DOWN, 0, d, d, kPackRows, 0, t.dyt};
-    VLA_CK(group(ps, 1, t.hb, Fp, D.F, t.xt, t.dxf, d));
+    ps[0] = Proj{VLA_PROJ_DOWN, 0, d, d, kPackRows, 0};
+    VLA_CK(group(ps, 1, t.hb, Fp, D.F, t.xt, t.dxf, d, t.dyt));
   }
   // dL/d(layer input) = dxm + RMSNorm backward of du1
-  if (l > 0) VLA_CK(launch_rmsnorm_bwd(xs, w.attn_norm, eps, t.du, t.dxm, t.dx, nullptr, M, d, s));
+  if (l > 0) VLA_CK(launch_rmsnorm_bwd(xs, w.attn_norm, eps, t.du, t.dxm, t.dx, t.dxf, M, d, s));
   return VLA_OK;
 }
 
@@ -1182,6 +1176,7 @@ int vla_ppo_lora_grads(vla_model* m, int32_t B, const void* vis, const int32_t* 
   VLA_CK(launch_rmsnorm_bwd(t.xc, m->final_norm, m->cfg.rms_eps, t.du_h, nullptr, t.dxc, nullptr, R, D.d, s));
   VLA_CK(launch_fill_zero(t.dx, (size_t)M * D.d * sizeof(float), s));
   VLA_CK(launch_move_rows(t.dxc, m->head_rows, R, D.d, t.dx, true, s));
+  VLA_CK(launch_to_frag(t.dx, D.d, M, D.d, D.d, t.dxf, s));
   for (int l = D.L - 1; l >= 0; --l) {
     rc = layer_backward(m, t, l, B, M, lora, s);
     if (rc) return rc;
