@@ -206,14 +206,18 @@ __global__ __launch_bounds__(256) void swiglu_bwd_kernel(const float* __restrict
 //   pass 1 (queries): a wave takes 16-query tiles; per 32-key chunk it forms
 //     S^T = K Q^T and dP^T = V dO^T, keys on the MFMA rows in the order that
 //     leaves lane group g holding keys 8g .. 8g+7 of the chunk, so dS^T is
-//     already the B operand of dQ^T += K^T dS^T.  V (key-major) and K^T (16-key
-//     pages) are transposed into LDS once; K rows stream from the cache.  Also
-//     writes D and dO rounded to bf16 (row-major) for pass 2.
+//     already the B operand of dQ^T += K^T dS^T.  Also writes D and dO rounded
+//     to bf16 (row-major) for pass 2.
 //   pass 2 (keys): a wave takes 16-key tiles; per 32-query chunk it forms
 //     S = Q K^T and dP = dO V^T with queries on the MFMA rows in the same
 //     order, so P and dS are the B operands of dV^T += dO^T P and
-//     dK^T += Q^T dS.  Q^T and dO^T (16-query pages) are transposed into LDS
-//     once; Q and dO rows stream from memory.
+//     dK^T += Q^T dS.
+// What a pass contracts over is copied into LDS once as it lies (K rows and V^T
+// pages; Q and dO rows), and each serves both of its products: one operand by
+// 16-byte reads, the transposed one by ds_read_b64_tr_b16.  Keeping only the
+// transposed tiles (made in registers) and streaming the row operands from
+// memory in the loop, 2 waves per SIMD waited on those loads: 16 x 295 rows of
+// 32 heads of 128, dQ 130 -> 96 us and dK, dV 200 -> 98 (16 heads of 64: 41 -> 31, 63 -> 31).
 // P and dS enter their products as hi + lo bf16 pairs (~16 significant bits);
 // q, k, v and dO are the bf16 operands of the forward.  q and k are the rotated
 // values the forward attended with: their gradients go back through the inverse
@@ -232,39 +236,49 @@ __device__ __forceinline__ int qk_packed_col(int f) {
 }
 // Row order of a key- (query-) major MFMA operand: row i of 16-row tile t of 32-row chunk c
 // is sequence row 32 c + 8 (i / 4) + 4 t + i % 4, so C rows 4 g + r of tiles t = 0, 1 are
-// rows 8 g .. 8 g + 7 of the chunk in lane group g.  ab_slot inverts it.
-__device__ __forceinline__ int ab_row(int R) { return 32 * (R >> 5) + 8 * ((R & 15) >> 2) + 4 * ((R >> 4) & 1) + (R & 3); }
-__device__ __forceinline__ int ab_slot(int k) {
-  const int w = k & 31;
-  return 32 * (k >> 5) + 16 * ((w >> 2) & 1) + 4 * (w >> 3) + (w & 3);
-}
-// 16-byte feature chunk j of LDS row R of a row-major tile is stored at chunk j ^ ab_swz(R)
+// rows 8 g .. 8 g + 7 of the chunk in lane group g.
+// 16-byte feature chunk j of row R of a row-major tile in LDS is stored at chunk j ^ ab_swz(R): the 16 rows of an MFMA
+// operand (in that order) lie on distinct banks.
 template <int HD>
 __device__ __forceinline__ int ab_swz(int R) {
-  return HD == 128 ? (R & 15) : ((R >> 1) & 7);
+  return HD == 128 ? ((R & 3) | (((R >> 3) & 3) << 2)) : (((R >> 1) & 1) | (((R >> 3) & 3) << 1));
 }
-// byte offset of (feature f, rows 8h .. 8h + 7 of a 16-row page) in a paged transposed tile:
-// half h of feature f sits at 16-byte unit 2 f + (h ^ ((f >> 3) & 1)) of its page
+// MFMA operand of 8 consecutive k by two transposed reads of 4 k x 16 rows: each group of 16 lanes hands in 16 x 8 bytes,
+// lane i those of k i / 4, rows 4 (i % 4) .. + 4, and lane i gets row i's 4 k.
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef short s16x8 __attribute__((ext_vector_type(8)));
+typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+__device__ __forceinline__ bf16x8 ab_tr(const char* lo, const char* hi) {
+  const s16x4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)lo);
+  const s16x4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)hi);
+  return __builtin_bit_cast(bf16x8, __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+// Operand row r16 of 16-row tile t of chunk c, features 32 ks + 8 g .., of a row-major tile.
 template <int HD>
-__device__ __forceinline__ int ab_page_off(int page, int f, int h) {
-  return page * (HD * kPage * 2) + 16 * (2 * f + (h ^ ((f >> 3) & 1)));
+__device__ __forceinline__ bf16x8 ab_rows(const char* tile, int c, int t, int r16, int g, int ks) {
+  const int R = 32 * c + 8 * (r16 >> 2) + 4 * t + (r16 & 3);
+  return as_bf16x8(*reinterpret_cast<const uint4*>(tile + R * (HD * 2) + 16 * ((4 * ks + g) ^ ab_swz<HD>(8 * (r16 >> 2) + (r16 & 3)))));
 }
-// transpose of an 8 x 8 bf16 block: out[b] element a = in[a] element b
-__device__ __forceinline__ void transpose8(const uint4* in, uint4* out) {
-  uint32_t w[32], o[32];
-#pragma unroll
-  for (int a = 0; a < 8; ++a) {
-    w[4 * a] = in[a].x; w[4 * a + 1] = in[a].y; w[4 * a + 2] = in[a].z; w[4 * a + 3] = in[a].w;
+// Operand of rows = features 16 nb .., k = rows 32 c + 8 g .. + 8 of a row-major tile.
+template <int HD>
+__device__ __forceinline__ bf16x8 ab_cols(const char* tile, int c, int r16, int g, int nb) {
+  const int r = 8 * g + (r16 >> 2);  // ab_swz does not depend on bit 2 of the row
+  const char* p = tile + (32 * c + r) * (HD * 2) + 16 * ((2 * nb + ((r16 >> 1) & 1)) ^ ab_swz<HD>(r)) + 8 * (r16 & 1);
+  return ab_tr(p, p + 4 * HD * 2);
+}
+// Copies rows 0 .. 32 nch of a row-major [.., ld] matrix (row r >= L: row L - 1) into a row-major tile, 1 KB per wave and
+// instruction; `page_base(r)`: where the rows of the 16-row page that holds row r begin.
+template <int HD, class F>
+__device__ __forceinline__ void ab_copy_rows(char* tile, int nch, int L, int ld, int wave, int lane, F page_base) {
+  constexpr int CH = HD / 8, RPK = 64 / CH;  // chunks of a row, rows of a copy
+  const uint32_t lb = (uint32_t)(uintptr_t)((lds_ptr_t*)tile);
+  for (int i = wave; i < 32 * nch / RPK; i += kAbWaves) {
+    const int r0 = min(i * RPK, L - 1) & ~(kPage - 1);  // the page of the copy's rows (they lie in one)
+    const int R = i * RPK + lane / CH, chunk = (lane % CH) ^ ab_swz<HD>(R);
+    const __amdgpu_buffer_rsrc_t rs =
+        __builtin_amdgcn_make_buffer_rsrc((void*)page_base(r0), (short)0, 0x7fffffff, 0x00020000);
+    lds_dma16(lb + i * 1024, (uint32_t)((min(R, L - 1) - r0) * ld + 8 * chunk) * 2, rs, 0);
   }
-#pragma unroll
-  for (int b = 0; b < 8; ++b)
-#pragma unroll
-    for (int ap = 0; ap < 4; ++ap) {
-      const uint32_t lo = w[8 * ap + b / 2], hi = w[8 * ap + 4 + b / 2];
-      o[4 * b + ap] = (b & 1) ? ((lo >> 16) | (hi & 0xffff0000u)) : ((lo & 0xffffu) | (hi << 16));
-    }
-#pragma unroll
-  for (int b = 0; b < 8; ++b) out[b] = make_uint4(o[4 * b], o[4 * b + 1], o[4 * b + 2], o[4 * b + 3]);
 }
 // element i of hi, lo = v as a hi + lo pair of bf16
 __device__ __forceinline__ void split_bf16(float v, bf16x8& hi, bf16x8& lo, int i) {
@@ -300,9 +314,9 @@ __device__ __forceinline__ void ab_store_rot(const AttnBwdArgs& a, size_t row, i
 
 // pass 1, one 16-query tile: queries 16 qt .. 16 qt + 15, keys in chunks 0 .. qt / 2
 template <int HD>
-__device__ __forceinline__ void ab_dq_tile(const AttnBwdArgs& a, const char* vlds, const char* ktlds, int ptv, int qt,
-                                           int L, int row0, int head, int lane) {
-  constexpr int KROW = HD * 2, KS = HD / 32, NB = HD / 16;
+__device__ __forceinline__ void ab_dq_tile(const AttnBwdArgs& a, const char* klds, const char* vlds, int qt, int L,
+                                           int row0, int head, int lane) {
+  constexpr int KS = HD / 32, NB = HD / 16, VPAGE = HD * kPage * 2;
   const int r16 = lane & 15, g = lane >> 4, H = a.n_heads;
   const int q = qt * 16 + r16;
   const size_t row = (size_t)(row0 + min(q, L - 1));
@@ -338,16 +352,15 @@ __device__ __forceinline__ void ab_dq_tile(const AttnBwdArgs& a, const char* vld
     for (int t = 0; t < 2; ++t) {
       s[t] = f32x4{0.f, 0.f, 0.f, 0.f};
       dp[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-      // A operand row r16 of tile t: key 32 c + 8 (r16 / 4) + 4 t + r16 % 4 (clamped into the sequence)
-      const int key = min(ab_row(32 * c + 16 * t + r16), L - 1);
-      const int page = __shfl(ptv, key / kPage, kWave);
-      const bf16_t* kp = a.kv.k + (((size_t)page * H + head) * kPage + key % kPage) * HD + 8 * g;
-      const char* vr = vlds + (32 * c + 16 * t + r16) * KROW;
+      // V rows of the same keys from V^T pages: features 32 ks + 8 g .., lane i hands in feature i / 4, keys 8 q + 4 t ..
+      // of the chunk for q = r16 % 4 (the keys of operand rows 4 q ..)
+      const int f = 8 * g + (r16 >> 2), q4 = r16 & 3;
+      const char* vp = vlds + (2 * c + (q4 >> 1)) * VPAGE + 8 * t;
+      const int u0 = (2 * f + (q4 & 1)) ^ ((g & 1) << 3), u1 = (2 * (f + 4) + (q4 & 1)) ^ ((g & 1) << 3);
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) {
-        s[t] = mfma16(as_bf16x8(*reinterpret_cast<const uint4*>(kp + 32 * ks)), as_bf16x8(qf[ks]), s[t]);
-        dp[t] = mfma16(as_bf16x8(*reinterpret_cast<const uint4*>(vr + 16 * ((4 * ks + g) ^ ab_swz<HD>(r16)))),
-                       as_bf16x8(df[ks]), dp[t]);
+        s[t] = mfma16(ab_rows<HD>(klds, c, t, r16, g, ks), as_bf16x8(qf[ks]), s[t]);
+        dp[t] = mfma16(ab_tr(vp + 16 * (64 * ks + u0), vp + 16 * (64 * ks + u1)), as_bf16x8(df[ks]), dp[t]);
       }
     }
     // lane: query q, keys 32 c + 8 g + 4 t + r -> dS^T as the B operand (hi + lo)
@@ -361,11 +374,10 @@ __device__ __forceinline__ void ab_dq_tile(const AttnBwdArgs& a, const char* vld
         const float ds = key <= q ? p * (dp[t][r] - dd) : 0.f;
         split_bf16(ds, shi, slo, 4 * t + r);
       }
-    // dQ^T += K^T dS^T: A operand = K^T rows 16 nb + r16, keys 32 c + 8 g .. + 8
-    const char* kt0 = ktlds + ab_page_off<HD>(2 * c + (g >> 1), r16, g & 1);
+    // dQ^T += K^T dS^T
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) {
-      const bf16x8 kv = as_bf16x8(*reinterpret_cast<const uint4*>(kt0 + nb * 512));
+      const bf16x8 kv = ab_cols<HD>(klds, c, r16, g, nb);
       dq[nb] = mfma16(kv, shi, dq[nb]);
       dq[nb] = mfma16(kv, slo, dq[nb]);
     }
@@ -374,57 +386,43 @@ __device__ __forceinline__ void ab_dq_tile(const AttnBwdArgs& a, const char* vld
 }
 
 template <int HD>
-__global__ __launch_bounds__(64 * kAbWaves, 1) void attn_bwd_dq_kernel(AttnBwdArgs a) {
-  constexpr int KROW = HD * 2, VPAGE = HD * kPage * 2, HC = HD / 8;
+__global__ __launch_bounds__(64 * kAbWaves, HD == 128 ? 2 : 4) void attn_bwd_dq_kernel(AttnBwdArgs a) {
+  constexpr int KROW = HD * 2, VPAGE = HD * kPage * 2;
   __shared__ __attribute__((aligned(1024))) char lds[kAbKeys * KROW + kAbPages * VPAGE];
-  char* const vlds = lds;                     // V, key-major rows in ab_row order
-  char* const ktlds = lds + kAbKeys * KROW;   // K^T, 16-key pages
+  char* const klds = lds;                   // K rows
+  char* const vlds = lds + kAbKeys * KROW;  // V^T, 16-key pages: 16-byte unit u of a page at u ^ 8 (u / 16 % 2)
   const int env = blockIdx.x, head = blockIdx.y, H = a.n_heads;
   const int L = a.env_len[env], row0 = a.env_row0[env];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int nch = (L + 31) / 32;
   const int32_t* pt = a.page_table + env * a.max_pages;
-  // fill: task (8-key group kg, feature chunk fc); keys >= L are zero
-  for (int i = threadIdx.x; i < nch * 4 * HC; i += 64 * kAbWaves) {
-    const int kg = i / HC, fc = i % HC, k0 = 8 * kg;
-    uint4 vin[8], kin[8], vout[8], kout[8];
-    if (k0 < L) {
-      const int page = pt[kg >> 1], h = kg & 1;
-      const bf16_t* vp = a.kv.v + (((size_t)page * H + head) * HD + 8 * fc) * kPage + 8 * h;
-      const bf16_t* kp = a.kv.k + (((size_t)page * H + head) * kPage + 8 * h) * HD + 8 * fc;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        vin[e] = *reinterpret_cast<const uint4*>(vp + e * kPage);            // feature 8 fc + e, keys k0 ..
-        kin[e] = k0 + e < L ? *reinterpret_cast<const uint4*>(kp + e * HD)  // key k0 + e, features 8 fc ..
-                            : make_uint4(0, 0, 0, 0);
-      }
-    } else {
-#pragma unroll
-      for (int e = 0; e < 8; ++e) vin[e] = kin[e] = make_uint4(0, 0, 0, 0);
-    }
-    transpose8(vin, vout);  // vout[b]: key k0 + b, features 8 fc ..
-    transpose8(kin, kout);  // kout[e]: feature 8 fc + e, keys k0 ..
-#pragma unroll
-    for (int b = 0; b < 8; ++b) {
-      const int R = ab_slot(k0 + b);
-      *reinterpret_cast<uint4*>(vlds + R * KROW + 16 * (fc ^ ab_swz<HD>(R))) =
-          k0 + b < L ? vout[b] : make_uint4(0, 0, 0, 0);
-      *reinterpret_cast<uint4*>(ktlds + ab_page_off<HD>(kg >> 1, 8 * fc + b, kg & 1)) = kout[b];
-    }
+  // the environment's page table, one entry per lane (<= 20 pages), waited for once (the copies below are not loads that
+  // the compiler knows)
+  int ptv = pt[min(lane, a.max_pages - 1)];
+  asm volatile("" : "+v"(ptv));
+  ab_copy_rows<HD>(klds, nch, L, HD, wave, lane, [&](int r) {
+    return a.kv.k + ((size_t)__builtin_amdgcn_readlane(ptv, r / kPage) * H + head) * kPage * HD;
+  });
+  const uint32_t vb = (uint32_t)(uintptr_t)((lds_ptr_t*)vlds);
+  for (int i = wave; i < 2 * nch * (VPAGE / 1024); i += kAbWaves) {
+    const int pg = min(i / (VPAGE / 1024), (L - 1) / kPage);  // past the sequence: keys that no query sees
+    const int p = i % (VPAGE / 1024) * 64 + lane, u = p ^ (((p >> 4) & 1) << 3);
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+        (void*)(a.kv.v + ((size_t)__builtin_amdgcn_readlane(ptv, pg) * H + head) * HD * kPage), (short)0, 0x7fffffff, 0x00020000);
+    lds_dma16(vb + i * 1024, 16 * u, rs, 0);
   }
-  // the environment's page table, one entry per lane (<= 20 pages)
-  const int ptv = pt[min(lane, a.max_pages - 1)];
+  __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
   const int nq = (L + 15) / 16;
   for (int p0 = 0; p0 < nq; p0 += kAbWaves) {  // most expensive tiles first, snake order
     const int p = p0 + (((p0 / kAbWaves) & 1) ? kAbWaves - 1 - wave : wave);
-    if (p < nq) ab_dq_tile<HD>(a, vlds, ktlds, ptv, nq - 1 - p, L, row0, head, lane);
+    if (p < nq) ab_dq_tile<HD>(a, klds, vlds, nq - 1 - p, L, row0, head, lane);
   }
 }
 
 // pass 2, one 16-key tile: keys 16 kt .. 16 kt + 15, queries in chunks kt / 2 .. nch - 1
 template <int HD>
-__device__ __forceinline__ void ab_dkv_tile(const AttnBwdArgs& a, const char* qtl, const char* otl, const int32_t* pt,
+__device__ __forceinline__ void ab_dkv_tile(const AttnBwdArgs& a, const char* qlds, const char* olds, const int32_t* pt,
                                             int kt, int L, int nch, int row0, int head, int lane) {
   constexpr int KS = HD / 32, NB = HD / 16;
   const int r16 = lane & 15, g = lane >> 4, H = a.n_heads;
@@ -449,18 +447,19 @@ __device__ __forceinline__ void ab_dkv_tile(const AttnBwdArgs& a, const char* qt
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb) dk[nb] = dv[nb] = f32x4{0.f, 0.f, 0.f, 0.f};
   for (int c = kt / 2; c < nch; ++c) {
+    float2 ld[8];  // (log-sum-exp, D) of the lane's 8 queries
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+      ld[e] = *reinterpret_cast<const float2*>(a.stats + ((size_t)(row0 + min(32 * c + 8 * g + e, L - 1)) * H + head) * 2);
     f32x4 s[2], dp[2];
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
       s[t] = f32x4{0.f, 0.f, 0.f, 0.f};
       dp[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-      // A operand row r16 of tile t: query 32 c + 8 (r16 / 4) + 4 t + r16 % 4 (clamped)
-      const int qi = min(ab_row(32 * c + 16 * t + r16), L - 1);
-      const size_t at = (size_t)(row0 + qi) * a.d + head * HD + 8 * g;
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) {
-        s[t] = mfma16(as_bf16x8(*reinterpret_cast<const uint4*>(a.q + at + 32 * ks)), as_bf16x8(kf[ks]), s[t]);
-        dp[t] = mfma16(as_bf16x8(*reinterpret_cast<const uint4*>(a.do16 + at + 32 * ks)), as_bf16x8(vf[ks]), dp[t]);
+        s[t] = mfma16(ab_rows<HD>(qlds, c, t, r16, g, ks), as_bf16x8(kf[ks]), s[t]);
+        dp[t] = mfma16(ab_rows<HD>(olds, c, t, r16, g, ks), as_bf16x8(vf[ks]), dp[t]);
       }
     }
     // lane: key `key`, queries 32 c + 8 g + 4 t + r -> P and dS as B operands (hi + lo)
@@ -470,20 +469,18 @@ __device__ __forceinline__ void ab_dkv_tile(const AttnBwdArgs& a, const char* qt
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int qq = 32 * c + 8 * g + 4 * t + r;
-        const float2 ld = *reinterpret_cast<const float2*>(a.stats + ((size_t)(row0 + min(qq, L - 1)) * H + head) * 2);
         const bool live = qq >= key && qq < L;
-        const float p = live ? expf(a.scale * s[t][r] - ld.x) : 0.f;
-        const float ds = live ? p * (dp[t][r] - ld.y) : 0.f;
+        const float p = live ? expf(a.scale * s[t][r] - ld[4 * t + r].x) : 0.f;
+        const float ds = live ? p * (dp[t][r] - ld[4 * t + r].y) : 0.f;
         split_bf16(p, phi, plo, 4 * t + r);
         split_bf16(ds, shi, slo, 4 * t + r);
       }
-    // dV^T += dO^T P, dK^T += Q^T dS: A operands = rows 16 nb + r16 of the transposed tiles,
-    // queries 32 c + 8 g .. + 8
-    const int off = ab_page_off<HD>(2 * c + (g >> 1), r16, g & 1);
+    // dV^T += dO^T P, dK^T += Q^T dS (their operands are not read ahead of the exponentials: the registers spill)
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) {
-      const bf16x8 ov = as_bf16x8(*reinterpret_cast<const uint4*>(otl + off + nb * 512));
-      const bf16x8 qv = as_bf16x8(*reinterpret_cast<const uint4*>(qtl + off + nb * 512));
+      const bf16x8 ov = ab_cols<HD>(olds, c, r16, g, nb);
+      const bf16x8 qv = ab_cols<HD>(qlds, c, r16, g, nb);
       dv[nb] = mfma16(ov, phi, dv[nb]);
       dv[nb] = mfma16(ov, plo, dv[nb]);
       dk[nb] = mfma16(qv, shi, dk[nb]);
@@ -502,41 +499,24 @@ __device__ __forceinline__ void ab_dkv_tile(const AttnBwdArgs& a, const char* qt
 }
 
 template <int HD>
-__global__ __launch_bounds__(64 * kAbWaves, 1) void attn_bwd_dkv_kernel(AttnBwdArgs a) {
-  constexpr int VPAGE = HD * kPage * 2, HC = HD / 8;
-  __shared__ __attribute__((aligned(1024))) char lds[2 * kAbPages * VPAGE];
-  char* const qtl = lds;                   // Q^T, 16-query pages
-  char* const otl = lds + kAbPages * VPAGE;  // dO^T (bf16), 16-query pages
+__global__ __launch_bounds__(64 * kAbWaves, 2) void attn_bwd_dkv_kernel(AttnBwdArgs a) {
+  constexpr int ROW = HD * 2;
+  __shared__ __attribute__((aligned(1024))) char lds[2 * kAbKeys * ROW];
+  char* const qlds = lds;                  // Q rows
+  char* const olds = lds + kAbKeys * ROW;  // dO rows (bf16)
   const int env = blockIdx.x, head = blockIdx.y;
   const int L = a.env_len[env], row0 = a.env_row0[env];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int nch = (L + 31) / 32;
-  // fill: task (8-query group kg, feature chunk fc); queries >= L are zero
-  for (int i = threadIdx.x; i < nch * 4 * HC; i += 64 * kAbWaves) {
-    const int kg = i / HC, fc = i % HC, t0 = 8 * kg;
-    uint4 qin[8], oin[8], qout[8], oout[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const size_t at = (size_t)(row0 + t0 + e) * a.d + head * HD + 8 * fc;
-      const bool in = t0 + e < L;
-      qin[e] = in ? *reinterpret_cast<const uint4*>(a.q + at) : make_uint4(0, 0, 0, 0);
-      oin[e] = in ? *reinterpret_cast<const uint4*>(a.do16 + at) : make_uint4(0, 0, 0, 0);
-    }
-    transpose8(qin, qout);
-    transpose8(oin, oout);
-#pragma unroll
-    for (int b = 0; b < 8; ++b) {
-      const int off = ab_page_off<HD>(kg >> 1, 8 * fc + b, kg & 1);
-      *reinterpret_cast<uint4*>(qtl + off) = qout[b];
-      *reinterpret_cast<uint4*>(otl + off) = oout[b];
-    }
-  }
+  ab_copy_rows<HD>(qlds, nch, L, a.d, wave, lane, [&](int r) { return a.q + (size_t)(row0 + r) * a.d + head * HD; });
+  ab_copy_rows<HD>(olds, nch, L, a.d, wave, lane, [&](int r) { return a.do16 + (size_t)(row0 + r) * a.d + head * HD; });
+  __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
   const int nq = (L + 15) / 16;
   const int32_t* pt = a.page_table + env * a.max_pages;
   for (int p0 = 0; p0 < nq; p0 += kAbWaves) {  // most expensive (earliest) key tiles first, snake order
     const int p = p0 + (((p0 / kAbWaves) & 1) ? kAbWaves - 1 - wave : wave);
-    if (p < nq) ab_dkv_tile<HD>(a, qtl, otl, pt, p, L, nch, row0, head, lane);
+    if (p < nq) ab_dkv_tile<HD>(a, qlds, olds, pt, p, L, nch, row0, head, lane);
   }
 }
 

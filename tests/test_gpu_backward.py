@@ -16,7 +16,7 @@ pytestmark = pytest.mark.gpu
 PROJ = ("wq", "wk", "wv", "wo", "wgate", "wup", "wdown")
 
 
-def _case(cfg, seed, rank=8, std=0.05, scale=0.5, layers_adapted=None, keys=PROJ):
+def _case(cfg, seed, rank=8, std=0.05, scale=0.5, layers_adapted=None, keys=PROJ, lens=None):
     S = Setup(cfg, seed=seed)
     L = cfg.n_layers
     full = inputs.make_lora(cfg, rank, seed=seed, device="cuda", std=std)
@@ -29,7 +29,7 @@ def _case(cfg, seed, rank=8, std=0.05, scale=0.5, layers_adapted=None, keys=PROJ
             bp = torch.zeros(b.shape[0], rp, dtype=b.dtype, device=b.device)
             ap[:rank], bp[:, :rank] = a, b
             S.model.lora_merge(li, k, S.w["layers"][li][k], ap, bp.contiguous(), scale)
-    inp, dev = S.inputs(seed=seed)
+    inp, dev = S.inputs(seed=seed) if lens is None else S.inputs(seed=seed, prompt_lens=lens)
     B, T, eps = inp.batch, 1.5, 0.2
     acts = torch.from_numpy(inputs.stored_actions(cfg, B, seed=seed)).cuda()
     tf = S.model.token_logprobs(dev["vis"], dev["ids"], inp.prompt_lens, acts, T)
@@ -117,6 +117,17 @@ def test_partial_adapters_and_odd_rank():
     stats, lp, grads, ref = _case(cfg, seed=43, rank=5, layers_adapted=[cfg.n_layers - 1], keys=("wq", "wv", "wdown"))
     assert all(not g for g in grads[:-1]) and set(grads[-1]) == {"wq", "wv", "wdown"}
     _check("tiny bwd partial", stats, lp, grads, ref, inputs.ppo_minibatch(cfg.batch, seed=43)[2], cfg.n_layers)
+
+
+@pytest.mark.parametrize("heads", [4, 2])
+def test_gradients_at_the_edges_of_the_attention_tiles(heads):
+    """head_dim 64 and 128, sequences that end at and beside the edges of 16-row tiles and 32-row chunks, the shortest of
+    one chunk and the longest (320 rows)."""
+    lens = [0, 1, 15, 16, 17, 31, 32, 288]  # 32 .. 320 rows
+    cfg = inputs.TINY.replace(name=f"bwd_edges{heads}", n_layers=1, n_heads=heads, n_visual=25, batch=len(lens),
+                              prompt_min=0, prompt_max=288)
+    stats, lp, grads, ref = _case(cfg, seed=53, lens=lens)
+    _check(f"bwd edges {heads} heads", stats, lp, grads, ref, inputs.ppo_minibatch(cfg.batch, seed=53)[2], cfg.n_layers)
 
 
 def test_mid_lora_gradients_match_oracle():
