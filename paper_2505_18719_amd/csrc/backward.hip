@@ -243,16 +243,6 @@ template <int HD>
 __device__ __forceinline__ int ab_swz(int R) {
   return HD == 128 ? ((R & 3) | (((R >> 3) & 3) << 2)) : (((R >> 1) & 1) | (((R >> 3) & 3) << 1));
 }
-// MFMA operand of 8 consecutive k by two transposed reads of 4 k x 16 rows: each group of 16 lanes hands in 16 x 8 bytes,
-// lane i those of k i / 4, rows 4 (i % 4) .. + 4, and lane i gets row i's 4 k.
-typedef short s16x4 __attribute__((ext_vector_type(4)));
-typedef short s16x8 __attribute__((ext_vector_type(8)));
-typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
-__device__ __forceinline__ bf16x8 ab_tr(const char* lo, const char* hi) {
-  const s16x4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)lo);
-  const s16x4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)hi);
-  return __builtin_bit_cast(bf16x8, __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7));
-}
 // Operand row r16 of 16-row tile t of chunk c, features 32 ks + 8 g .., of a row-major tile.
 template <int HD>
 __device__ __forceinline__ bf16x8 ab_rows(const char* tile, int c, int t, int r16, int g, int ks) {
@@ -264,7 +254,7 @@ template <int HD>
 __device__ __forceinline__ bf16x8 ab_cols(const char* tile, int c, int r16, int g, int nb) {
   const int r = 8 * g + (r16 >> 2);  // ab_swz does not depend on bit 2 of the row
   const char* p = tile + (32 * c + r) * (HD * 2) + 16 * ((2 * nb + ((r16 >> 1) & 1)) ^ ab_swz<HD>(r)) + 8 * (r16 & 1);
-  return ab_tr(p, p + 4 * HD * 2);
+  return lds_read_tr(p, p + 4 * HD * 2);
 }
 // Copies rows 0 .. 32 nch of a row-major [.., ld] matrix (row r >= L: row L - 1) into a row-major tile, 1 KB per wave and
 // instruction; `page_base(r)`: where the rows of the 16-row page that holds row r begin.
@@ -360,7 +350,7 @@ __device__ __forceinline__ void ab_dq_tile(const AttnBwdArgs& a, const char* kld
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) {
         s[t] = mfma16(ab_rows<HD>(klds, c, t, r16, g, ks), as_bf16x8(qf[ks]), s[t]);
-        dp[t] = mfma16(ab_tr(vp + 16 * (64 * ks + u0), vp + 16 * (64 * ks + u1)), as_bf16x8(df[ks]), dp[t]);
+        dp[t] = mfma16(lds_read_tr(vp + 16 * (64 * ks + u0), vp + 16 * (64 * ks + u1)), as_bf16x8(df[ks]), dp[t]);
       }
     }
     // lane: query q, keys 32 c + 8 g + 4 t + r -> dS^T as the B operand (hi + lo)

@@ -98,6 +98,16 @@ __host__ __device__ __forceinline__ size_t frag_index(int r, int k, int K) {
 
 typedef __attribute__((address_space(3))) void lds_ptr_t;
 
+// MFMA operand of 8 consecutive k by two transposed reads of 4 k x 16 rows: each group of 16 lanes hands in 16 x 8 bytes
+// of LDS, lane i those of k i / 4, rows 4 (i % 4) .. + 4, and lane i gets row i's 4 k.
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+__device__ __forceinline__ bf16x8 lds_read_tr(const char* lo, const char* hi) {
+  const s16x4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)lo);
+  const s16x4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)hi);
+  return __builtin_bit_cast(bf16x8, __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+
 // s_waitcnt with vmcnt <= n (n < 64) and the other counters unconstrained.
 #define WAIT_VMCNT(n) __builtin_amdgcn_s_waitcnt((((n) >> 4) << 14) | (0xF << 8) | (0x7 << 4) | ((n) & 15))
 

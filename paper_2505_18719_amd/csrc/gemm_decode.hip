@@ -41,26 +41,35 @@ using skinny::COLS;
 using skinny::NW;
 using skinny::UNIT_K;
 
-template <int MB>
+template <int MB, bool T>
 __global__ __launch_bounds__(64 * NW, 1) void skinny_kernel(SkinnyArgs a, SkinnyPlan p) {
-  extern __shared__ float red[];  // [NW][MB*16][COLS]
+  extern __shared__ __attribute__((aligned(1024))) float red[];  // [NW][MB*16][COLS], T: then the waves' weight blocks
   const skinny::Sched sc = skinny::make_sched(p, blockIdx.x);
   skinny::Ring<MB> r;
-  skinny::run<MB, false>(sc, a, p, r, red, false);
+  skinny::run<MB, false, T>(sc, a, p, r, red, false);
 }
 
-template <int MB>
+template <int MB, bool T>
 hipError_t launch_mb(const SkinnyArgs& a, const SkinnyPlan& p, hipStream_t st) {
-  const size_t lds = skinny::red_bytes<MB>();
+  const size_t lds = skinny::red_bytes<MB>() + (T ? skinny::kTransposeBytes : 0);
   static bool attr_set = false;  // dynamic LDS above 64 KB must be allowed once per kernel
   if (!attr_set && lds > 65536) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&skinny_kernel<MB>),
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&skinny_kernel<MB, T>),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     attr_set = true;
   }
-  hipLaunchKernelGGL((skinny_kernel<MB>), dim3(p.G), dim3(64 * NW), lds, st, a, p);
+  hipLaunchKernelGGL((skinny_kernel<MB, T>), dim3(p.G), dim3(64 * NW), lds, st, a, p);
   return hipGetLastError();
+}
+
+template <bool T>
+hipError_t launch_rows(const SkinnyArgs& a, const SkinnyPlan& p, hipStream_t st) {
+  const int mb = (a.M + 15) / 16;
+  if (mb <= 1) return launch_mb<1, T>(a, p, st);
+  if (mb <= 2) return launch_mb<2, T>(a, p, st);
+  if (mb <= 4) return launch_mb<4, T>(a, p, st);
+  return launch_mb<8, T>(a, p, st);
 }
 
 }  // namespace
@@ -86,11 +95,19 @@ hipError_t launch_skinny(const SkinnyArgs& a, const SkinnyPlan& p, hipStream_t s
   if (a.M > 128 || a.N % COLS != 0 || a.K % UNIT_K != 0 || p.tiles != a.N / COLS ||
       p.chunks != a.K / UNIT_K || p.G < 1 || (long long)frag_elems(a.N, a.K) * 2 >= (1ll << 31))
     return hipErrorInvalidValue;
-  const int mb = (a.M + 15) / 16;
-  if (mb <= 1) return launch_mb<1>(a, p, st);
-  if (mb <= 2) return launch_mb<2>(a, p, st);
-  if (mb <= 4) return launch_mb<4>(a, p, st);
-  return launch_mb<8>(a, p, st);
+  return launch_rows<false>(a, p, st);
+}
+
+// C = A W with W [kt, ldw] as it lies (the gradients' products over the rows of an activation matrix): the same units, slots
+// and sums as launch_skinny with a transposed copy of W, which cost a pass of its own (the twelve of a 4720-row layer's
+// gradients at d = 4096 225 us), at the time of the untransposed product (64 rows x 22016, 4720 rows: 46 us for 47).
+hipError_t launch_skinny_t(const SkinnyArgs& a, const SkinnyPlan& p, hipStream_t st) {
+  if (a.M <= 0 || a.N <= 0) return hipSuccess;
+  if (a.M > 128 || a.N % COLS != 0 || a.K % UNIT_K != 0 || p.tiles != a.N / COLS || p.chunks != a.K / UNIT_K || p.G < 1 ||
+      a.kt < 1 || a.kt > a.K || a.ldw % 32 != 0 || a.col0 < 0 || a.col0 % 32 != 0 || a.col0 + a.N > a.ldw ||
+      (long long)frag_elems(a.kt, a.ldw) * 2 >= (1ll << 31) || (long long)frag_elems(a.M, a.K) * 2 >= (1ll << 31))
+    return hipErrorInvalidValue;
+  return launch_rows<true>(a, p, st);
 }
 
 }  // namespace vla

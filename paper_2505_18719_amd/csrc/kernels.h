@@ -86,6 +86,9 @@ struct SkinnyArgs {
   const bf16_t* W;  // [N, K] in frag layout
   int N, K;
   float* part;      // [plan.slots, M, N]
+  // launch_skinny_t: W holds the contraction along its rows, [kt, ldw] in frag layout with the N columns from col0 on
+  // (col0 % 32 == 0); rows from kt up to K count as zeros, whatever W's last row block holds there
+  int kt, ldw, col0;
 };
 struct SkinnyPlan {
   int tiles;     // N / 64
@@ -139,6 +142,7 @@ __device__ inline float skinny_sum(const float* __restrict__ part, const SkinnyP
 // The plan for `workgroups` workgroups, with fewer if needed to keep every tile within `max_slots`.
 SkinnyPlan skinny_plan(int N, int K, int workgroups, int max_slots);
 hipError_t launch_skinny(const SkinnyArgs& a, const SkinnyPlan& p, hipStream_t s);
+hipError_t launch_skinny_t(const SkinnyArgs& a, const SkinnyPlan& p, hipStream_t s);
 
 // Persistent decode layer (decode_layer.hip): everything of a decoder layer
 // after attention at one decode step, plus the next projection, in one

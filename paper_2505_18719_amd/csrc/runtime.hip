@@ -528,7 +528,7 @@ struct TrainBufs {
   SavedActs sv;  // what the forward keeps per layer
   float *dx, *dxm, *du, *dob, *xm, *cgu, *dh, *stats, *dz, *du_h, *xc, *dxc, *logp, *dlogp;
   float* spart;  // skinny-GEMM partials
-  bf16_t *dxf, *dxmf, *u1, *ob, *u2, *hb, *dgu, *dqkv, *wt, *xt, *dyt, *dzf, *wact_t, *apk, *bpt, *t1f, *t2f, *do16;
+  bf16_t *dxf, *dxmf, *u1, *ob, *u2, *hb, *dgu, *dqkv, *wt, *dzf, *wact_t, *apk, *bpt, *t1f, *t2f, *do16;
 };
 
 // keep: every layer's activations are kept by the forward (no recompute in the backward)
@@ -586,8 +586,6 @@ void plan_train(Layout& L, const Dims& D, TrainBufs& t, bool keep) {
   t.do16 = L.take<bf16_t>(Mx * d);
   t.wt = L.take<bf16_t>(std::max(std::max(frag_elems(D.Fp, D.d), frag_elems(D.d, 2 * D.Fp)),
                                  std::max(frag_elems(D.d, D.d), frag_elems(D.d, 3 * D.d))));
-  t.xt = L.take<bf16_t>(frag_elems(std::max(D.d, D.Fp), Mk));
-  t.dyt = L.take<bf16_t>(frag_elems(std::max(3 * D.d, 2 * D.Fp), Mk));
   t.dzf = L.take<bf16_t>(frag_elems(Rh, A32));
   t.wact_t = L.take<bf16_t>(frag_elems(D.d, A32));
   t.apk = L.take<bf16_t>(frag_elems(128, std::max(D.d, D.Fp)));
@@ -661,23 +659,27 @@ int layer_backward(vla_model* m, TrainBufs& t, int l, int B, int M, const vla_lo
   // contractions over the M rows run with K = Mk, rows past M zero):
   //   T1^T = A X^T, T2^T = B^T dY^T (r x M);  dB^T = T1^T dY,  dA = T2^T X.
   // Projections that share X and dY (q, k, v; gate, up) stack their A and B^T
-  // factors, 16-row aligned, into one operand, so X, dY and X^T stream once per
-  // group for T1, T2 and dA.
+  // factors, 16-row aligned, into one operand, so X and dY stream twice per group.
+  // The products over the rows read X and dY as they lie (launch_skinny_t).
   auto adapted = [&](int p) { return lora->a[l * 7 + p] != nullptr; };
   SkinnyPlan sp{};  // of the last skinny GEMM, whose slots are in t.spart
   auto skinny_to = [&](const bf16_t* a_op, int rows, const bf16_t* w_op, int N, int K) {
     sp = skinny_plan(N, K, m->cus, kMaxSplits);
     return launch_skinny(SkinnyArgs{a_op, rows, w_op, N, K, t.spart}, sp, s);
   };
+  // T [rows, M] times columns col0 .. col0 + N of the row-wise matrix Y [M, ky]
+  auto skinny_rows = [&](const bf16_t* t_op, int rows, const bf16_t* Y, int ky, int col0, int N) {
+    sp = skinny_plan(N, Mk, m->cus, kMaxSplits);
+    return launch_skinny_t(SkinnyArgs{t_op, rows, Y, N, Mk, t.spart, M, ky, col0}, sp, s);
+  };
   const int r16 = round_up(lora->rank, 16), per = 128 / r16;
   // one projection of a group: its packed output columns o0 .. o0 + n_cols of dY (the order of `mode`)
   struct Proj {
     int p, o0, n_cols, out, mode, part;
   };
-  // X frag [M, kx] (in real input features) with X^T rows in64 (XT); dY frag [M, ky] with dY^T rows (dYT).  The factors of
-  // up to 128 stacked rows run together; each product's slots go straight into what reads them.
-  auto group = [&](const Proj* ps, int n, const bf16_t* X, int kx, int in, const bf16_t* XT, const bf16_t* dY, int ky,
-                   const bf16_t* dYT) -> hipError_t {
+  // X frag [M, kx] (in real input features), dY frag [M, ky].  The factors of up to 128 stacked rows run together; each
+  // product's slots go straight into what reads them.
+  auto group = [&](const Proj* ps, int n, const bf16_t* X, int kx, int in, const bf16_t* dY, int ky) -> hipError_t {
     hipError_t e;
     for (int b0 = 0; b0 < n; b0 += per) {
       LoraGroup lg{std::min(per, n - b0), r16, {}};
@@ -697,16 +699,10 @@ int layer_backward(vla_model* m, TrainBufs& t, int l, int B, int M, const vla_lo
       if ((e = launch_reduce_frag(t.spart, sp, rows, M, Mk, t.t1f, s)) != hipSuccess) return e;
       if ((e = skinny_to(t.bpt, rows, dY, Mp, ky)) != hipSuccess) return e;
       if ((e = launch_reduce_frag(t.spart, sp, rows, M, Mk, t.t2f, s)) != hipSuccess) return e;
-      // dB of all projections from one pass over their columns of dY^T, where the skinny GEMM's offsets reach
-      const bool whole = (long long)frag_elems(col1 - col0, Mk) * 2 < (1ll << 31);
-      for (int i = 0; i < (whole ? 1 : lg.n); ++i) {
-        const LoraGroup q = whole ? lg : LoraGroup{1, r16, {lg.p[i]}};
-        const int c0 = whole ? col0 : q.p[0].o0, c1 = whole ? col1 : c0 + q.p[0].n_cols;
-        if ((e = skinny_to(t.t1f + frag_index(i * r16, 0, Mk), q.n * r16, dYT + frag_index(c0, 0, Mk), c1 - c0, Mk)) != hipSuccess)
-          return e;
-        if ((e = launch_lora_finalize(q, t.spart, sp, true, c0, s)) != hipSuccess) return e;
-      }
-      if ((e = skinny_to(t.t2f, rows, XT, round_up(in, 64), Mk)) != hipSuccess) return e;
+      // dB of all projections from one pass over their columns of dY
+      if ((e = skinny_rows(t.t1f, rows, dY, ky, col0, col1 - col0)) != hipSuccess) return e;
+      if ((e = launch_lora_finalize(lg, t.spart, sp, true, col0, s)) != hipSuccess) return e;
+      if ((e = skinny_rows(t.t2f, rows, X, kx, 0, round_up(in, 64))) != hipSuccess) return e;
       if ((e = launch_lora_finalize(lg, t.spart, sp, false, 0, s)) != hipSuccess) return e;
     }
     return hipSuccess;
@@ -716,30 +712,18 @@ int layer_backward(vla_model* m, TrainBufs& t, int l, int B, int M, const vla_lo
   for (int p = VLA_PROJ_Q; p <= VLA_PROJ_V; ++p)
     if (adapted(p))
       ps[n++] = Proj{p, p * d, d, d, p == VLA_PROJ_V ? kPackRows : kPackQk, 0};
-  if (n) {
-    VLA_CK(launch_transpose_frag(u1, false, d, M, d, Mk, t.xt, s));
-    VLA_CK(launch_transpose_frag(t.dqkv, false, 3 * d, M, 3 * d, Mk, t.dyt, s));
-    VLA_CK(group(ps, n, u1, d, d, t.xt, t.dqkv, 3 * d, t.dyt));
-  }
+  if (n) VLA_CK(group(ps, n, u1, d, d, t.dqkv, 3 * d));
   if (adapted(VLA_PROJ_O)) {
-    VLA_CK(launch_transpose_frag(ob, false, d, M, d, Mk, t.xt, s));
-    VLA_CK(launch_transpose_frag(t.dxmf, false, d, M, d, Mk, t.dyt, s));
     ps[0] = Proj{VLA_PROJ_O, 0, d, d, kPackRows, 0};
-    VLA_CK(group(ps, 1, ob, d, d, t.xt, t.dxmf, d, t.dyt));
+    VLA_CK(group(ps, 1, ob, d, d, t.dxmf, d));
   }
   n = 0;
   for (int p = VLA_PROJ_GATE; p <= VLA_PROJ_UP; ++p)
     if (adapted(p)) ps[n++] = Proj{p, 0, Fg, D.F, kPackGateUp, p - VLA_PROJ_GATE};
-  if (n) {
-    VLA_CK(launch_transpose_frag(u2, false, d, M, d, Mk, t.xt, s));
-    VLA_CK(launch_transpose_frag(t.dgu, false, 2 * Fp, M, Fg, Mk, t.dyt, s));
-    VLA_CK(group(ps, n, u2, d, d, t.xt, t.dgu, 2 * Fp, t.dyt));
-  }
+  if (n) VLA_CK(group(ps, n, u2, d, d, t.dgu, 2 * Fp));
   if (adapted(VLA_PROJ_DOWN)) {
-    VLA_CK(launch_transpose_frag(t.hb, false, Fp, M, D.F, Mk, t.xt, s));
-    VLA_CK(launch_transpose_frag(t.dxf, false, d, M, d, Mk, t.dyt, s));
     ps[0] = Proj{VLA_PROJ_DOWN, 0, d, d, kPackRows, 0};
-    VLA_CK(group(ps, 1, t.hb, Fp, D.F, t.xt, t.dxf, d, t.dyt));
+    VLA_CK(group(ps, 1, t.hb, Fp, D.F, t.dxf, d));
   }
   // dL/d(layer input) = dxm + RMSNorm backward of du1
   if (l > 0) VLA_CK(launch_rmsnorm_bwd(xs, w.attn_norm, eps, t.du, t.dxm, t.dx, t.dxf, M, d, s));

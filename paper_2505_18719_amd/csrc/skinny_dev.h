@@ -125,7 +125,12 @@ __device__ __forceinline__ void prefetch_w(const Sched& sc, const SkinnyArgs& a,
 // prefetch_w.  SC1: partial sums are written through to memory (sc1 stores), so
 // that workgroups of other XCDs can read them after a grid barrier without a
 // cache write-back.
-template <int MB, bool SC1>
+//
+// T: the weights lie transposed (SkinnyArgs::kt): a unit's 256 x 64 block is 16 x 2 frag blocks, a wave takes the 4 x 2 of
+// its K step whole, puts them into its 8 KB of LDS (after `red`) and reads its operands from there transposed.
+constexpr size_t kTransposeBytes = (size_t)NW * 8192;
+
+template <int MB, bool SC1, bool T = false>
 __device__ __forceinline__ void run(const Sched& sc, const SkinnyArgs& a, const SkinnyPlan& p, Ring<MB>& r,
                                     float* red, bool prefetched) {
   constexpr int D = ring_depth<MB>(), DX = x_ring_depth<MB>();
@@ -183,12 +188,46 @@ __device__ __forceinline__ void run(const Sched& sc, const SkinnyArgs& a, const 
   auto ldw = [&](int i, uint4 (&wv)[4][2]) {
     int chunk;
     const int tile = sc.unit_tile(min(i, total - 1), chunk);
+    if constexpr (T) {  // wv[rb][cb]: row block rb of the K step, 32-column block cb of the tile
+      const int last = (a.kt + 15) / 16 - 1, KBW = frag_kb(a.ldw);
+#pragma unroll
+      for (int rb = 0; rb < 4; ++rb)
+#pragma unroll
+        for (int cb = 0; cb < 2; ++cb)
+          wv[rb][cb] = as_uint4(__builtin_amdgcn_raw_buffer_load_b128(
+              rsW, loff, (min(16 * chunk + 4 * wave + rb, last) * KBW + a.col0 / 32 + 2 * tile + cb) * 1024, 0));
+      return;
+    }
     const int kb = 8 * chunk + 2 * wave;
 #pragma unroll
     for (int nb = 0; nb < 4; ++nb)
 #pragma unroll
       for (int h = 0; h < 2; ++h)
         wv[nb][h] = as_uint4(__builtin_amdgcn_raw_buffer_load_b128(rsW, loff, ((tile * 4 + nb) * KB + kb + h) * 1024, 0));
+  };
+  // T: the loaded blocks of unit i become its operands
+  char* const wt = reinterpret_cast<char*>(red) + red_bytes<MB>() + wave * 8192;
+  auto transpose_w = [&](int i, uint4 (&wv)[4][2]) {
+    int chunk;
+    (void)sc.unit_tile(i, chunk);
+    const int k0 = UNIT_K * chunk + 64 * wave;
+    if (k0 + 64 > a.kt) {  // the end of the contraction: rows past it
+#pragma unroll
+      for (int rb = 0; rb < 4; ++rb)
+        if (k0 + 16 * rb + r16 >= a.kt) wv[rb][0] = wv[rb][1] = make_uint4(0, 0, 0, 0);
+    }
+#pragma unroll
+    for (int rb = 0; rb < 4; ++rb)
+#pragma unroll
+      for (int cb = 0; cb < 2; ++cb) *reinterpret_cast<uint4*>(wt + (2 * rb + cb) * 1024 + 16 * lane) = wv[rb][cb];
+    const char* p = wt + 2048 * (g4 >> 1) + 16 * (8 * (g4 & 1) + (r16 >> 2)) + 256 * ((r16 >> 1) & 1) + 8 * (r16 & 1);
+#pragma unroll
+    for (int nb = 0; nb < 4; ++nb)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const char* q = p + 4096 * h + 1024 * (nb >> 1) + 512 * (nb & 1);
+        wv[nb][h] = __builtin_bit_cast(uint4, lds_read_tr(q, q + 64));
+      }
   };
   auto ldx = [&](int i, uint4 (&xv)[MB][2]) {
     int chunk;
@@ -223,6 +262,7 @@ __device__ __forceinline__ void run(const Sched& sc, const SkinnyArgs& a, const 
       ldw(i + D - 1, r.w[(j + D - 1) % D]);
       SKINNY_PIN();
       if (i < total) {
+        if constexpr (T) transpose_w(i, r.w[j % D]);
 #pragma unroll
         for (int h = 0; h < 2; ++h)
 #pragma unroll

@@ -130,6 +130,32 @@ def test_gradients_at_the_edges_of_the_attention_tiles(heads):
     _check(f"bwd edges {heads} heads", stats, lp, grads, ref, inputs.ppo_minibatch(cfg.batch, seed=53)[2], cfg.n_layers)
 
 
+@pytest.mark.parametrize("mode", [vla.TRAIN_KEEP, vla.TRAIN_RECOMPUTE])
+@pytest.mark.parametrize("lens", [[3], [0, 9, 30], [57] * 4])
+def test_gradients_do_not_depend_on_what_the_workspace_held(mode, lens):
+    """Row counts off the 16- and 64-row edges of the products over the rows: the padding of their last row block may
+    hold NaN (the workspace filled with 0xff) without reaching a gradient."""
+    cfg = inputs.TINY.replace(name="bwd_ws", batch=len(lens), prompt_min=0, prompt_max=57)
+    S = Setup(cfg, seed=54)
+    ad = inputs.make_lora(cfg, 16, seed=54, device="cuda")
+    inp, dev = S.inputs(seed=54, prompt_lens=lens)
+    B = inp.batch
+    acts = torch.from_numpy(inputs.stored_actions(cfg, B, seed=54)).cuda()
+    old = S.model.token_logprobs(dev["vis"], dev["ids"], inp.prompt_lens, acts, 1.5)["logp"]
+    adv = torch.from_numpy(inputs.ppo_minibatch(B, seed=54)[2]).cuda()
+
+    def run():
+        out = S.model.ppo_lora_grads(dev["vis"], dev["ids"], inp.prompt_lens, acts, old, adv, 0.2, 1.5, ad, 0.5, mode=mode)
+        torch.cuda.synchronize()
+        return [g.clone() for layer in out[2] for k in PROJ for g in layer[k]]
+
+    first = run()
+    S.model._train_ws.fill_(255)
+    for a, b in zip(first, run()):
+        assert torch.isfinite(b).all() and torch.equal(a, b)
+    S.model.close()
+
+
 def test_mid_lora_gradients_match_oracle():
     """Mid decoder (8 layers, d 1024, 16 heads): the gradient through eight layers."""
     cfg = inputs.MID.replace(batch=2)
