@@ -41,35 +41,35 @@ using skinny::COLS;
 using skinny::NW;
 using skinny::UNIT_K;
 
-template <int MB, bool T>
+template <int MB, bool T, bool S>
 __global__ __launch_bounds__(64 * NW, 1) void skinny_kernel(SkinnyArgs a, SkinnyPlan p) {
   extern __shared__ __attribute__((aligned(1024))) float red[];  // [NW][MB*16][COLS], T: then the waves' weight blocks
   const skinny::Sched sc = skinny::make_sched(p, blockIdx.x);
   skinny::Ring<MB> r;
-  skinny::run<MB, false, T>(sc, a, p, r, red, false);
+  skinny::run<MB, false, T, S>(sc, a, p, r, red, false);
 }
 
-template <int MB, bool T>
+template <int MB, bool T, bool S>
 hipError_t launch_mb(const SkinnyArgs& a, const SkinnyPlan& p, hipStream_t st) {
   const size_t lds = skinny::red_bytes<MB>() + (T ? skinny::kTransposeBytes : 0);
   static bool attr_set = false;  // dynamic LDS above 64 KB must be allowed once per kernel
   if (!attr_set && lds > 65536) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&skinny_kernel<MB, T>),
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&skinny_kernel<MB, T, S>),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     attr_set = true;
   }
-  hipLaunchKernelGGL((skinny_kernel<MB, T>), dim3(p.G), dim3(64 * NW), lds, st, a, p);
+  hipLaunchKernelGGL((skinny_kernel<MB, T, S>), dim3(p.G), dim3(64 * NW), lds, st, a, p);
   return hipGetLastError();
 }
 
-template <bool T>
+template <bool T, bool S>
 hipError_t launch_rows(const SkinnyArgs& a, const SkinnyPlan& p, hipStream_t st) {
   const int mb = (a.M + 15) / 16;
-  if (mb <= 1) return launch_mb<1, T>(a, p, st);
-  if (mb <= 2) return launch_mb<2, T>(a, p, st);
-  if (mb <= 4) return launch_mb<4, T>(a, p, st);
-  return launch_mb<8, T>(a, p, st);
+  if (mb <= 1) return launch_mb<1, T, S>(a, p, st);
+  if (mb <= 2) return launch_mb<2, T, S>(a, p, st);
+  if (mb <= 4) return launch_mb<4, T, S>(a, p, st);
+  return launch_mb<8, T, S>(a, p, st);
 }
 
 }  // namespace
@@ -95,7 +95,7 @@ hipError_t launch_skinny(const SkinnyArgs& a, const SkinnyPlan& p, hipStream_t s
   if (a.M > 128 || a.N % COLS != 0 || a.K % UNIT_K != 0 || p.tiles != a.N / COLS ||
       p.chunks != a.K / UNIT_K || p.G < 1 || (long long)frag_elems(a.N, a.K) * 2 >= (1ll << 31))
     return hipErrorInvalidValue;
-  return launch_rows<false>(a, p, st);
+  return a.stream ? launch_rows<false, true>(a, p, st) : launch_rows<false, false>(a, p, st);
 }
 
 // C = A W with W [kt, ldw] as it lies (the gradients' products over the rows of an activation matrix): the same units, slots
@@ -107,7 +107,7 @@ hipError_t launch_skinny_t(const SkinnyArgs& a, const SkinnyPlan& p, hipStream_t
       a.kt < 1 || a.kt > a.K || a.ldw % 32 != 0 || a.col0 < 0 || a.col0 % 32 != 0 || a.col0 + a.N > a.ldw ||
       (long long)frag_elems(a.kt, a.ldw) * 2 >= (1ll << 31) || (long long)frag_elems(a.M, a.K) * 2 >= (1ll << 31))
     return hipErrorInvalidValue;
-  return launch_rows<true>(a, p, st);
+  return launch_rows<true, false>(a, p, st);
 }
 
 }  // namespace vla

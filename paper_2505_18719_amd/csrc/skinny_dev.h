@@ -126,11 +126,12 @@ __device__ __forceinline__ void prefetch_w(const Sched& sc, const SkinnyArgs& a,
 // that workgroups of other XCDs can read them after a grid barrier without a
 // cache write-back.
 //
+// NT: the weights are loaded non-temporally.
 // T: the weights lie transposed (SkinnyArgs::kt): a unit's 256 x 64 block is 16 x 2 frag blocks, a wave takes the 4 x 2 of
 // its K step whole, puts them into its 8 KB of LDS (after `red`) and reads its operands from there transposed.
 constexpr size_t kTransposeBytes = (size_t)NW * 8192;
 
-template <int MB, bool SC1, bool T = false>
+template <int MB, bool SC1, bool T = false, bool NT = false>
 __device__ __forceinline__ void run(const Sched& sc, const SkinnyArgs& a, const SkinnyPlan& p, Ring<MB>& r,
                                     float* red, bool prefetched) {
   constexpr int D = ring_depth<MB>(), DX = x_ring_depth<MB>();
@@ -203,7 +204,8 @@ __device__ __forceinline__ void run(const Sched& sc, const SkinnyArgs& a, const 
     for (int nb = 0; nb < 4; ++nb)
 #pragma unroll
       for (int h = 0; h < 2; ++h)
-        wv[nb][h] = as_uint4(__builtin_amdgcn_raw_buffer_load_b128(rsW, loff, ((tile * 4 + nb) * KB + kb + h) * 1024, 0));
+        wv[nb][h] = as_uint4(
+            __builtin_amdgcn_raw_buffer_load_b128(rsW, loff, ((tile * 4 + nb) * KB + kb + h) * 1024, NT ? 2 : 0));
   };
   // T: the loaded blocks of unit i become its operands
   char* const wt = reinterpret_cast<char*>(red) + red_bytes<MB>() + wave * 8192;
