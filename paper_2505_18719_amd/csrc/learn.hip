@@ -230,9 +230,10 @@ __global__ __launch_bounds__(256) void logprob_backward_kernel(LogprobBwdArgs a)
 }
 
 // The same with 16 lanes per row and float4 loads and stores (bins % 4 == 0, 16-byte aligned rows): 4 KB of logits in
-// flight per wave, 4-step trees for four rows at once where the kernel above runs 6-step ones for one, and z / T - max / T
-// as one fused multiply-add with 1 / T where it divides (the division's and expf's instructions, not memory, bounded it:
-// 458752 x 256 305 us = 3.1 TB/s -> 157 us = 6.0 TB/s).
+// flight per wave, 4-step trees for four rows at once where the kernel above runs 6-step ones for one, and (z - max) times
+// 1 / T where it divides (the division's and expf's instructions, not memory, bounded it: 458752 x 256 305 us = 3.1 TB/s
+// -> 157 us = 6.0 TB/s).  The maximum is taken off before the scaling: its exponent is 0 whatever max / T is, where a fused
+// z / T - round(max / T) leaves the rounding error of max / T, which past |max / T| = 2^31 is more than expf's range.
 __global__ __launch_bounds__(256) void logprob_backward4_kernel(LogprobBwdArgs a) {
   const int row = blockIdx.x * 16 + (threadIdx.x >> 4);
   const int l = threadIdx.x & 15, lim4 = a.bins / 4;
@@ -251,13 +252,12 @@ __global__ __launch_bounds__(256) void logprob_backward4_kernel(LogprobBwdArgs a
 #pragma unroll
   for (int u = 0; u < 4; ++u) m = fmaxf(m, fmaxf(fmaxf(v[u][0], v[u][1]), fmaxf(v[u][2], v[u][3])));
   m = row_max16(m);
-  const float mt = m * inv_t;
   float su[4];
 #pragma unroll
   for (int u = 0; u < 4; ++u) {
     const bool live = l + 16 * u < lim4;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) v[u][e] = live ? expf(fmaf(v[u][e], inv_t, -mt)) : 0.f;
+    for (int e = 0; e < 4; ++e) v[u][e] = live ? expf((v[u][e] - m) * inv_t) : 0.f;
     su[u] = (v[u][0] + v[u][1]) + (v[u][2] + v[u][3]);
   }
   const float se = row_sum16((su[0] + su[1]) + (su[2] + su[3]));
@@ -300,7 +300,8 @@ hipError_t launch_ppo_clip(const PpoArgs& a, hipStream_t s) {
 hipError_t launch_logprob_backward(const LogprobBwdArgs& a, hipStream_t s) {
   if (a.rows <= 0) return hipSuccess;
   if (a.bins <= 0 || a.bins > 256) return hipErrorInvalidValue;
-  // float4 rows, and a temperature whose reciprocal is a normal number far from the ends of the range
+  // float4 rows, and a temperature whose reciprocal is a normal number and so small that where z - max overflows to -inf,
+  // its exponential is 0 anyway
   const uintptr_t align = reinterpret_cast<uintptr_t>(a.logits) | reinterpret_cast<uintptr_t>(a.dlogits);
   if (a.bins % 4 == 0 && align % 16 == 0 && a.temperature >= 0x1p-100f && a.temperature <= 0x1p100f)
     hipLaunchKernelGGL(logprob_backward4_kernel, dim3((a.rows + 15) / 16), dim3(256), 0, s, a);

@@ -185,6 +185,28 @@ def test_logprob_backward_of_whole_float4_rows(rows, bins):
         assert np.all(x[:, 1:3] == 0) and np.all(np.abs(x - ref) <= 32 * U32 * (1 / 0.7 + np.abs(ref)))
 
 
+@pytest.mark.parametrize("T,scale", [(1e-9, 1.3), (1e-20, 1.3), (2.0 ** -100, 1.3), (1.5, 1e10), (0.01, 1e30), (2.0 ** 100, 1e30)])
+def test_logprob_backward_where_logits_dwarf_the_temperature(T, scale):
+    """Logits / T far past expf's range give finite gradients from both kernels (whole float4 rows, and rows that are not
+    16-byte aligned): the largest logit's exponent is 0.  Some bins are masked by -inf or the lowest finite value."""
+    T, rows, bins = float(np.float32(T)), 200, 256
+    rng = np.random.default_rng(17)
+    z = (scale * rng.normal(size=(rows, bins))).astype(np.float32)
+    z[::3, 1:3] = -np.inf
+    z[1::3, 5:9] = np.finfo(np.float32).min
+    best = z.argmax(1)
+    tok = np.where(np.arange(rows) % 2 == 0, best, rng.integers(0, bins, size=rows)).astype(np.int32)
+    dl = rng.normal(size=rows).astype(np.float32)
+    ref = lo.logprob_grad(z, tok, 0, T, dl)
+    zt, kt, dt = [torch.from_numpy(x).cuda() for x in (z, tok, dl)]
+    odd = torch.empty(rows * bins + 1, device="cuda")[1:].view(rows, bins)
+    for name, x in (("float4", zt), ("unaligned", odd.copy_(zt))):
+        got = vla.logprob_backward(x, kt, 0, T, dt).cpu().numpy()
+        assert np.isfinite(got).all(), (name, int((~np.isfinite(got)).any(1).sum()))
+        # p is 0 or 1 where the logits dwarf T, and within a few units of itself (see _bwd_check) in the last case
+        assert np.all(np.abs(got - ref) <= 32 * U32 * (np.abs(dl)[:, None] / T + np.abs(ref))), name
+
+
 def test_logprob_backward_out_of_range_token_gives_a_nan_row():
     _bwd_check(9, 256, 1.0, seed=3, bad_row=4)
 
