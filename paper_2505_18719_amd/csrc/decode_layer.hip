@@ -32,6 +32,7 @@
 // its next barrier, and raises VLA_FLAG_SYNC_TIMEOUT in the flags word.
 #include "common.h"
 #include "kernels.h"
+#include "lds_limit.h"
 #include "skinny_dev.h"
 
 namespace vla {
@@ -227,13 +228,9 @@ __global__ __launch_bounds__(64 * NW, 1) void decode_layer_kernel(DecodeLayerArg
 template <int MB>
 hipError_t launch_mb(const DecodeLayerArgs& a, int G, hipStream_t s) {
   const size_t lds = skinny::red_bytes<MB>();
-  static bool attr_set = false;
-  if (!attr_set && lds > 65536) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&decode_layer_kernel<MB>),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-    attr_set = true;
-  }
+  static LdsLimit limit;
+  const hipError_t e = limit.allow(reinterpret_cast<const void*>(&decode_layer_kernel<MB>), lds);
+  if (e != hipSuccess) return e;
   DecodeLayerArgs arg = a;
   void* args[] = {&arg};
   return hipLaunchCooperativeKernel(reinterpret_cast<const void*>(&decode_layer_kernel<MB>), dim3(G), dim3(64 * NW),

@@ -8,6 +8,7 @@
 #include "common.h"
 #include "embed_dev.h"
 #include "kernels.h"
+#include "lds_limit.h"
 
 namespace vla {
 
@@ -291,13 +292,9 @@ template <int NJ, int RPW>
 hipError_t launch_norm_frag(const float* x, int ldx, const int32_t* rows, const float* g, float eps, bf16_t* u,
                             int M, int d, hipStream_t s) {
   const size_t lds = (size_t)RPW * (2 * d + 16);
-  static bool attr_set = false;  // dynamic LDS above 64 KB must be allowed once per kernel
-  if (!attr_set) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&rmsnorm_frag_kernel<NJ, RPW>),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)(RPW * (2 * 256 * NJ + 16)));
-    if (e != hipSuccess) return e;
-    attr_set = true;
-  }
+  static LdsLimit limit;
+  const hipError_t e = limit.allow(reinterpret_cast<const void*>(&rmsnorm_frag_kernel<NJ, RPW>), RPW * (2 * 256 * NJ + 16));
+  if (e != hipSuccess) return e;
   hipLaunchKernelGGL((rmsnorm_frag_kernel<NJ, RPW>), dim3((M + RPW - 1) / RPW), dim3(64 * RPW), lds, s, x, ldx, rows,
                      g, eps, u, M, d);
   return hipGetLastError();

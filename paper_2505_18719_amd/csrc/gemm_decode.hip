@@ -31,6 +31,7 @@
 
 #include "common.h"
 #include "kernels.h"
+#include "lds_limit.h"
 #include "skinny_dev.h"
 
 namespace vla {
@@ -52,13 +53,9 @@ __global__ __launch_bounds__(64 * NW, 1) void skinny_kernel(SkinnyArgs a, Skinny
 template <int MB, bool T, bool S>
 hipError_t launch_mb(const SkinnyArgs& a, const SkinnyPlan& p, hipStream_t st) {
   const size_t lds = skinny::red_bytes<MB>() + (T ? skinny::kTransposeBytes : 0);
-  static bool attr_set = false;  // dynamic LDS above 64 KB must be allowed once per kernel
-  if (!attr_set && lds > 65536) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&skinny_kernel<MB, T, S>),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-    attr_set = true;
-  }
+  static LdsLimit limit;
+  const hipError_t e = limit.allow(reinterpret_cast<const void*>(&skinny_kernel<MB, T, S>), lds);
+  if (e != hipSuccess) return e;
   hipLaunchKernelGGL((skinny_kernel<MB, T, S>), dim3(p.G), dim3(64 * NW), lds, st, a, p);
   return hipGetLastError();
 }

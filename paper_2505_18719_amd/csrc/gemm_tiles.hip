@@ -16,6 +16,7 @@
 
 #include "common.h"
 #include "kernels.h"
+#include "lds_limit.h"
 
 namespace vla {
 
@@ -313,13 +314,9 @@ __global__ __launch_bounds__(T::NT) void gemm_tiles_kernel(GemmArgs a, int tiles
 
 template <class T, int EPI>
 hipError_t launch_shape_epi(const GemmArgs& a, hipStream_t s) {
-  static bool attr_set = false;  // dynamic LDS above 64 KB must be allowed once per kernel
-  if (!attr_set && T::LDS > 65536) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_tiles_kernel<T, EPI>),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, T::LDS);
-    if (e != hipSuccess) return e;
-    attr_set = true;
-  }
+  static LdsLimit limit;
+  const hipError_t e = limit.allow(reinterpret_cast<const void*>(&gemm_tiles_kernel<T, EPI>), T::LDS);
+  if (e != hipSuccess) return e;
   const int tm = (a.M + T::TM - 1) / T::TM, tn = (a.N + T::TN - 1) / T::TN;
   const int gm = std::max(1, std::min(tm, 1024 / T::TM));
   hipLaunchKernelGGL((gemm_tiles_kernel<T, EPI>), dim3(tm * tn), dim3(T::NT), T::LDS, s, a, tm, tn, gm);
