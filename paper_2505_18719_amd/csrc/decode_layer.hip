@@ -271,8 +271,7 @@ hipError_t launch_decode_layer(const DecodeLayerArgs& a, int G, hipStream_t s) {
   for (int i = 0; i < 4; ++i) {
     const SkinnyArgs& g = *gs[i];
     const SkinnyPlan& p = *ps[i];
-    if (g.M != a.M || g.N % skinny::COLS != 0 || g.K % skinny::UNIT_K != 0 || p.tiles != g.N / skinny::COLS ||
-        p.chunks != g.K / skinny::UNIT_K || p.G < 1 || (long long)frag_elems(g.N, g.K) * 2 >= (1ll << 31))
+    if (g.M != a.M || !skinny_plan_ok(p, g.N, g.K) || (long long)frag_elems(g.N, g.K) * 2 >= (1ll << 31))
       return hipErrorInvalidValue;
   }
   if (a.o.K != a.d || a.gu.K != a.d || a.dn.K != a.Fp || a.nx.K != a.d) return hipErrorInvalidValue;

@@ -75,7 +75,7 @@ SkinnyPlan skinny_plan(int N, int K, int workgroups, int max_slots) {
   SkinnyPlan p{};
   p.tiles = N / COLS;
   p.chunks = K / UNIT_K;
-  for (int G = workgroups; G >= 1; --G) {
+  for (int G = std::min(workgroups, kSkinnyMaxGroups); G >= 1; --G) {
     p.G = G;
     p.dp_tiles = (p.tiles / G) * G;
     const int U = (p.tiles - p.dp_tiles) * p.chunks;
@@ -89,8 +89,7 @@ SkinnyPlan skinny_plan(int N, int K, int workgroups, int max_slots) {
 
 hipError_t launch_skinny(const SkinnyArgs& a, const SkinnyPlan& p, hipStream_t st) {
   if (a.M <= 0 || a.N <= 0) return hipSuccess;
-  if (a.M > 128 || a.N % COLS != 0 || a.K % UNIT_K != 0 || p.tiles != a.N / COLS ||
-      p.chunks != a.K / UNIT_K || p.G < 1 || (long long)frag_elems(a.N, a.K) * 2 >= (1ll << 31))
+  if (a.M > 128 || !skinny_plan_ok(p, a.N, a.K) || (long long)frag_elems(a.N, a.K) * 2 >= (1ll << 31))
     return hipErrorInvalidValue;
   return a.stream ? launch_rows<false, true>(a, p, st) : launch_rows<false, false>(a, p, st);
 }
@@ -100,8 +99,8 @@ hipError_t launch_skinny(const SkinnyArgs& a, const SkinnyPlan& p, hipStream_t s
 // gradients at d = 4096 225 us), at the time of the untransposed product (64 rows x 22016, 4720 rows: 46 us for 47).
 hipError_t launch_skinny_t(const SkinnyArgs& a, const SkinnyPlan& p, hipStream_t st) {
   if (a.M <= 0 || a.N <= 0) return hipSuccess;
-  if (a.M > 128 || a.N % COLS != 0 || a.K % UNIT_K != 0 || p.tiles != a.N / COLS || p.chunks != a.K / UNIT_K || p.G < 1 ||
-      a.kt < 1 || a.kt > a.K || a.ldw % 32 != 0 || a.col0 < 0 || a.col0 % 32 != 0 || a.col0 + a.N > a.ldw ||
+  if (a.M > 128 || !skinny_plan_ok(p, a.N, a.K) || a.kt < 1 || a.kt > a.K || a.ldw % 32 != 0 || a.col0 < 0 ||
+      a.col0 % 32 != 0 || a.col0 + a.N > a.ldw ||
       (long long)frag_elems(a.kt, a.ldw) * 2 >= (1ll << 31) || (long long)frag_elems(a.M, a.K) * 2 >= (1ll << 31))
     return hipErrorInvalidValue;
   return launch_rows<true, false>(a, p, st);

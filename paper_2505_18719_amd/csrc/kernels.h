@@ -140,7 +140,14 @@ __device__ inline float4 sum_slots4(const float* __restrict__ p, size_t stride, 
 __device__ inline float skinny_sum(const float* __restrict__ part, const SkinnyPlan& p, int M, int N, int m, int n) {
   return sum_slots(part + (size_t)m * N + n, (size_t)M * N, skinny_slots(p, n >> 6), 0.f);
 }
-// The plan for `workgroups` workgroups, with fewer if needed to keep every tile within `max_slots`.
+// What the launches ask of a plan: that it is one of this product, and small enough for the 32-bit unit arithmetic above.
+inline bool skinny_plan_ok(const SkinnyPlan& p, int N, int K) {
+  return N % 64 == 0 && K % 256 == 0 && p.tiles == N / 64 && p.chunks == K / 256 && p.G >= 1 &&
+         (long long)p.tiles * p.chunks <= (1ll << 30) / p.G;
+}
+// The plan for `workgroups` workgroups, with fewer if needed to keep every tile within `max_slots` (and at most
+// kSkinnyMaxGroups, which N * K <= 2^30 leaves skinny_plan_ok).
+constexpr int kSkinnyMaxGroups = 1 << 14;
 SkinnyPlan skinny_plan(int N, int K, int workgroups, int max_slots);
 hipError_t launch_skinny(const SkinnyArgs& a, const SkinnyPlan& p, hipStream_t s);
 hipError_t launch_skinny_t(const SkinnyArgs& a, const SkinnyPlan& p, hipStream_t s);

@@ -73,7 +73,7 @@ __device__ __forceinline__ Sched make_sched(const SkinnyPlan& p, int g) {
   s.dp_tiles = p.dp_tiles;
   s.n_dp = (p.dp_tiles / p.G) * p.chunks;
   s.U = (p.tiles - p.dp_tiles) * p.chunks;
-  // N * K < 2^30 bounds U by 2^16, so these products stay below 2^31 (as those of skinny_owner)
+  // skinny_plan_ok keeps tiles * chunks * G within 2^30, and with it these products (as those of skinny_owner)
   s.su0 = (int)((unsigned)(g * s.U) / (unsigned)p.G);
   const int su1 = (int)((unsigned)((g + 1) * s.U) / (unsigned)p.G);
   s.total = g < p.G ? s.n_dp + (su1 - s.su0) : 0;

@@ -127,6 +127,30 @@ def test_learning_entry_points_validate_on_the_host(vla):
     assert lib.vla_logprob_backward(4, 256, 0, p, None, 1.5, p, p, None) == -1
 
 
+class _SkinnyPlan(ctypes.Structure):
+    _fields_ = [(n, ctypes.c_int) for n in ("tiles", "chunks", "G", "dp_tiles", "slots")]
+
+
+@pytest.mark.parametrize("N,K,workgroups", [(30000 * 64, 512, 40000), (32000 * 64, 512, 1 << 30), (4096, 11008, 256),
+                                            (12288, 4096, 256), (16000 * 64, 1024, 20000), (64, 256, 100000)])
+def test_decode_gemm_plan_stays_in_32_bit_units(vla, N, K, workgroups):
+    """The decode GEMM's kernels form (workgroup + 1) * units and unit * workgroups in 32 bits: no plan goes past them,
+    whatever number of workgroups is asked for, and each tile's closed-form slot count is the one of exact arithmetic."""
+    plan = vla.load_library()["_ZN3vla11skinny_planEiiii"]
+    plan.restype, plan.argtypes = _SkinnyPlan, [ctypes.c_int] * 4
+    p = plan(N, K, workgroups, 16)
+    assert (p.tiles, p.chunks) == (N // 64, K // 256) and 1 <= p.G <= workgroups
+    assert p.dp_tiles == p.tiles // p.G * p.G
+    U = (p.tiles - p.dp_tiles) * p.chunks
+    assert U == 0 or U >= p.G
+    assert (U + 1) * p.G + U < 2 ** 31
+    slots = 1
+    for t in range(p.tiles - p.dp_tiles):
+        first, last = (((u + 1) * p.G + U - 1) // U - 1 for u in (t * p.chunks, (t + 1) * p.chunks - 1))
+        slots = max(slots, last - first + 1)
+    assert p.slots == slots <= 16
+
+
 def test_extract_actions_validates_on_the_host(vla):
     lib = vla.load_library()
     p = ctypes.c_void_p(16)  # never dereferenced: validation fails first
