@@ -350,30 +350,27 @@ hipError_t launch_reduce_swiglu(const float* part, const SkinnyPlan& p, bf16_t* 
   return hipGetLastError();
 }
 
-// LoRA merge, one 256-thread workgroup per kMergeRows rows x kMergeCols K columns.  Rows are
+// LoRA merge, one 256-thread workgroup per kMergeRows rows x COLS K columns.  Rows are
 // the projection's own rows in packed order: for the interleaved [gate; up]
 // weight only the 32-row halves of `part`, so no workgroup computes rows it
 // does not write.  The update is taken transposed, A^T B^T on MFMA, a 16-row block of the projection in the columns of
 // the product and K columns 8 (i / 4) + 4 t + i % 4 of a 32-column block in row i of its tiles t = 0, 1: lane (row
 // l % 16, K elements 8 (l / 16) ..) then holds the update of the 16 bytes that it holds in frag layout, so the original
 // weights are loaded to that layout, the update is added in registers, and every store is a whole 1 KB block.  A^T of the
-// tile's columns is staged in LDS; B's rows are MFMA operands as they lie.
-// The merge is a copy with an update: tiles 128 columns wide, taken along the rows of the original weights, read 256-byte
-// pieces of rows that other workgroups are reading on, and the stores, which nothing reads soon, bypass the caches.  All
-// projections of the 7B shape at rank 32 (810 MB): 182 us (64 x 64 tiles taken down the columns, the update staged in
-// LDS) -> 170 -> 163 us with those stores = 5.0 TB/s, what a plain copy reaches; 128 x 128 tiles 166, 64 x 256 227, several
-// row steps per workgroup with the next one's loads in flight 175-190, loads that bypass the caches as well 176.
-constexpr int kMergeRows = 64, kMergeCols = 128;
+// tile's columns is staged in LDS; B's rows are MFMA operands as they lie.  The merge is a copy with an update, its tiles
+// taken along the rows of the original weights; NT stores bypass the caches.  Width and stores: launch_lora_merge_batch.
+constexpr int kMergeRows = 64;
 
 // Rows of the projection a merge computes (for [gate; up], the part's half of the packed rows).
 __host__ __device__ inline int merge_rows(const MergeArgs& a) { return a.mode == kPackGateUp ? a.rows / 2 : a.rows; }
 
-// Tile (rows kMergeRows rb .., columns kMergeCols cb ..) of one merge.
+// Tile (rows kMergeRows rb .., columns COLS cb ..) of one merge.
+template <int COLS, bool NT>
 __device__ __forceinline__ void merge_tile(const MergeArgs& a, int rb, int cb) {
-  constexpr int RB = kMergeRows / 64, CB = kMergeCols / 32;             // 16-row blocks of a wave, 32-column blocks
-  __shared__ __attribute__((aligned(16))) bf16_t at[kMergeCols][72];  // A^T: [column][rank], padded rows
+  constexpr int RB = kMergeRows / 64, CB = COLS / 32;              // 16-row blocks of a wave, 32-column blocks
+  __shared__ __attribute__((aligned(16))) bf16_t at[COLS][72];  // A^T: [column][rank], padded rows
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, r16 = lane & 15, g = lane >> 4;
-  const int c0 = cb * kMergeCols, nblk = min(kMergeCols, a.K - c0) / 32;
+  const int c0 = cb * COLS, nblk = min(COLS, a.K - c0) / 32;
   const int RK = (a.rank + 31) / 32 * 32;
   const bool gu = a.mode == kPackGateUp;
   const int nrows = merge_rows(a);
@@ -403,8 +400,8 @@ __device__ __forceinline__ void merge_tile(const MergeArgs& a, int rb, int cb) {
   }
   // A^T of the tile's columns, zero past the rank and past the source columns: 8 columns of one rank row per
   // 16-byte load
-  for (int e = tid; e < RK * (kMergeCols / 8); e += 256) {
-    const int kr = e / (kMergeCols / 8), c = 8 * (e % (kMergeCols / 8));
+  for (int e = tid; e < RK * (COLS / 8); e += 256) {
+    const int kr = e / (COLS / 8), c = 8 * (e % (COLS / 8));
     uint4 v = make_uint4(0, 0, 0, 0);
     if (kr < a.rank && c0 + c < a.src_cols) v = *reinterpret_cast<const uint4*>(a.a + (size_t)kr * a.src_cols + c0 + c);
     const uint32_t vv[4] = {v.x, v.y, v.z, v.w};
@@ -440,21 +437,23 @@ __device__ __forceinline__ void merge_tile(const MergeArgs& a, int rb, int cb) {
 #pragma unroll
         for (int x = 0; x < 8; ++x) w[x] += a.scale * acc[x >> 2][x & 3];
       }
-      const uint4 ov = make_uint4(pack2bf(w[0], w[1]), pack2bf(w[2], w[3]), pack2bf(w[4], w[5]), pack2bf(w[6], w[7]));
-      __builtin_nontemporal_store(__builtin_bit_cast(u32x4, ov),
-                                  reinterpret_cast<u32x4*>(a.dst + frag_index(row[i], col, a.K)));
+      const u32x4 ov = {pack2bf(w[0], w[1]), pack2bf(w[2], w[3]), pack2bf(w[4], w[5]), pack2bf(w[6], w[7])};
+      u32x4* const dst = reinterpret_cast<u32x4*>(a.dst + frag_index(row[i], col, a.K));
+      if constexpr (NT) __builtin_nontemporal_store(ov, dst);
+      else *dst = ov;
     }
   }
 }
 
 // One workgroup per tile of each item, the items' tiles one after the other, along the rows of the original weights.
+template <int COLS, bool NT>
 __global__ __launch_bounds__(256) void lora_merge_kernel(MergeBatch b) {
   int i = 0;
   while (i + 1 < b.n && (int)blockIdx.x >= b.wg0[i + 1]) ++i;
   const MergeArgs& a = b.item[i];
   const int local = (int)blockIdx.x - b.wg0[i];
-  const int ncb = (a.K + kMergeCols - 1) / kMergeCols;
-  merge_tile(a, local / ncb, local % ncb);
+  const int ncb = (a.K + COLS - 1) / COLS;
+  merge_tile<COLS, NT>(a, local / ncb, local % ncb);
 }
 
 static bool merge_ok(const MergeArgs& a) {
@@ -462,25 +461,60 @@ static bool merge_ok(const MergeArgs& a) {
          (a.mode != kPackGateUp || (a.part >= 0 && a.part <= 1 && a.rows % 64 == 0));
 }
 
-hipError_t launch_lora_merge_batch(MergeBatch b, hipStream_t s) {
-  if (b.n < 1 || b.n > kMergeBatchMax) return hipErrorInvalidValue;
+// Sets the first workgroup of each item for tiles of COLS columns; returns the launch's workgroups.
+static int merge_tiles(MergeBatch& b, int cols) {
   int wg = 0;
   for (int i = 0; i < b.n; ++i) {
-    if (b.item[i].rows < 0 || !merge_ok(b.item[i])) return hipErrorInvalidValue;
     b.wg0[i] = wg;
-    wg += (merge_rows(b.item[i]) + kMergeRows - 1) / kMergeRows * ((b.item[i].K + kMergeCols - 1) / kMergeCols);
+    wg += (merge_rows(b.item[i]) + kMergeRows - 1) / kMergeRows * ((b.item[i].K + cols - 1) / cols);
   }
-  b.wg0[b.n] = wg;
+  return b.wg0[b.n] = wg;
+}
+
+// The stores go past the caches where the merged weights and the original ones together do not fit the last-level cache
+// (`stream`, decided for the whole model: see vla_create).  A merge of one layer and a prefill of one environment, past the
+// caches / through them: d = 2560 (157 MB) 202 / 218 us, d = 4096 424 / 445; d = 2048 (101 MB) 145 / 139, d = 1536 112 / 110.
+// The merge of the 7B layer at rank 32 (810 MB) takes 158 us so = 5.1 TB/s, what a plain copy reaches.
+//
+// 128 columns instead of 64 (with such stores, us, 128 / 64):
+// - up to rank 32; above, a workgroup's staging of A^T costs more than the longer pieces of rows save (rank 64: d = 4096
+//   205 / 207, d = 3072 117 / 84, d = 1024 20 / 15);
+// - from 4096 workgroups on, or from 1024 on where the rows of an original weight are a multiple of 2 KB: there the 128 bytes
+//   of consecutive rows that 64 columns take presumably lie on few memory channels.  Merge of all layers and a prefill at rank 8:
+//   d = 4096, two layers 786 / 803, d = 3072 517 / 531, d = 1024, eight layers 647 / 662, but d = 1280 803 / 792.  Too few
+//   workgroups (the projections of d = 1024 one by one): 906 / 826.
+// Before, every merge ran 64 columns down the rows through an LDS tile with cached stores: d = 256 4.9 us (now 4.3), 1024
+// 13.5 (12.3), 2048 39 (35), 4096 180 (154) at rank 8.
+constexpr int kMergeWide = 4096, kMergeWideEven = 1024;
+hipError_t launch_lora_merge_batch(MergeBatch b, hipStream_t s) {
+  if (b.n < 1 || b.n > kMergeBatchMax) return hipErrorInvalidValue;
+  int rank = 0;
+  bool even = false;
+  for (int i = 0; i < b.n; ++i) {
+    if (b.item[i].rows < 0 || !merge_ok(b.item[i])) return hipErrorInvalidValue;
+    rank = std::max(rank, b.item[i].rank);
+    even |= b.item[i].src_ld % 1024 == 0;
+  }
+  if (b.stream && rank <= 32) {
+    const int wg = merge_tiles(b, 128);
+    if (wg >= (even ? kMergeWideEven : kMergeWide)) {
+      hipLaunchKernelGGL((lora_merge_kernel<128, true>), dim3(wg), dim3(256), 0, s, b);
+      return hipGetLastError();
+    }
+  }
+  const int wg = merge_tiles(b, 64);
   if (wg == 0) return hipSuccess;
-  hipLaunchKernelGGL(lora_merge_kernel, dim3(wg), dim3(256), 0, s, b);
+  if (b.stream) hipLaunchKernelGGL((lora_merge_kernel<64, true>), dim3(wg), dim3(256), 0, s, b);
+  else hipLaunchKernelGGL((lora_merge_kernel<64, false>), dim3(wg), dim3(256), 0, s, b);
   return hipGetLastError();
 }
 
-hipError_t launch_lora_merge(const MergeArgs& a, hipStream_t s) {
+hipError_t launch_lora_merge(const MergeArgs& a, bool stream, hipStream_t s) {
   if (a.rows <= 0) return hipSuccess;
   MergeBatch b{};
   b.item[0] = a;
   b.n = 1;
+  b.stream = stream;
   return launch_lora_merge_batch(b, s);
 }
 

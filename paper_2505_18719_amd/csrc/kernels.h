@@ -336,7 +336,8 @@ struct MergeArgs {
   int rank;
   float scale;
 };
-hipError_t launch_lora_merge(const MergeArgs& a, hipStream_t s);
+// stream: the merged weights are stored past the caches
+hipError_t launch_lora_merge(const MergeArgs& a, bool stream, hipStream_t s);
 // Up to seven merges (e.g. every projection of one layer) in one launch; each
 // item as launch_lora_merge requires it, item results as if merged one by one.
 constexpr int kMergeBatchMax = 7;
@@ -344,6 +345,7 @@ struct MergeBatch {
   MergeArgs item[kMergeBatchMax];
   int wg0[kMergeBatchMax + 1];  // first workgroup of each item; wg0[n] = the launch's workgroups
   int n;
+  bool stream;  // as for launch_lora_merge
 };
 hipError_t launch_lora_merge_batch(MergeBatch b, hipStream_t s);
 // Value head: values[r] = sum_k u[r, k] * head[k] for R rows of u (bf16,

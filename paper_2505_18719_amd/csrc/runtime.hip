@@ -162,7 +162,8 @@ struct vla_model {
   // decode GEMM work splits (one persistent workgroup per CU)
   SkinnyPlan plan_qkv, plan_o, plan_gu, plan_d, plan_head;
   int cus;  // compute units: the skinny GEMM's persistent grid
-  bool stream_w;  // decode reads the layers' weights past the caches
+  bool stream_w;      // decode reads the layers' weights past the caches
+  bool stream_merge;  // merges store them past the caches
   // persistent decode layer kernel: its buffers, and whether the device runs it
   float *part_o, *part_gu, *part_dn, *part_nx;  // split-K partials of each projection of a layer launch
   bf16_t *dec_ua, *dec_ub;                      // [Bmax, d] frag: MLP norm output, next norm output
@@ -781,8 +782,11 @@ int vla_create(const vla_config* cfg, const vla_weights* w, void* workspace, siz
     // only displaces what is read again (7B width, four layers, one environment: decode 2545 -> 2425 us; eight layers, 64
     // environments 8900 -> 8855); where they fit (mid preset, 200 MB) the next step finds them (1930 us, past the caches
     // 1996).
-    m->stream_w = (size_t)D.L * (frag_elems(4 * D.d, D.d) + frag_elems(2 * D.Fp, D.d) + frag_elems(D.d, D.Fp)) * sizeof(bf16_t) >
-                  (size_t)256 << 20;
+    const size_t layers = D.L * (frag_elems(4 * D.d, D.d) + frag_elems(2 * D.Fp, D.d) + frag_elems(D.d, D.Fp)) * sizeof(bf16_t);
+    m->stream_w = layers > (size_t)256 << 20;
+    // A merge of every layer reads as much again, the original weights: where both do not fit that cache, what is merged
+    // first is gone before anything reads it.
+    m->stream_merge = 2 * layers > (size_t)256 << 20;
     m->plan_qkv = skinny_plan(3 * D.d, D.d, cus, kMaxSplits);
     m->plan_o = skinny_plan(D.d, D.d, cus, kMaxSplits);
     m->plan_gu = skinny_plan(2 * D.Fp, D.d, cus, kMaxSplits);
@@ -1074,7 +1078,7 @@ int vla_lora_merge(vla_model* m, int32_t layer, int32_t projection, const void* 
   MergeArgs a;
   const int rc = merge_args(m, layer, projection, w0, lora_a, lora_b, rank, scale, &a);
   if (rc) return rc;
-  VLA_CK(launch_lora_merge(a, static_cast<hipStream_t>(stream)));
+  VLA_CK(launch_lora_merge(a, m->stream_merge, static_cast<hipStream_t>(stream)));
   g_err.clear();
   return VLA_OK;
 }
@@ -1084,6 +1088,7 @@ int vla_lora_merge_layer(vla_model* m, int32_t layer, const void* const* w0, con
   if (!m) return fail(VLA_EINVAL, "model is NULL");
   if (!w0 || !lora_a || !lora_b) return fail(VLA_EINVAL, "NULL array");
   MergeBatch b{};
+  b.stream = m->stream_merge;
   for (int32_t p = VLA_PROJ_Q; p <= VLA_PROJ_DOWN; ++p) {
     if (!w0[p]) continue;  // this projection is not merged
     const int rc = merge_args(m, layer, p, w0[p], lora_a[p], lora_b[p], rank, scale, &b.item[b.n]);

@@ -215,6 +215,27 @@ def test_lora_merge_layer_gives_the_bits_of_the_separate_merges(tiny):
         _assert_same_packed(cfg, w, _read_packed(S.model, cfg, w, 1), before[w], "a zero update restores the layer")
 
 
+@pytest.mark.parametrize("rank", [8, 64])
+def test_lora_merge_tile_widths_give_the_same_bits(rank):
+    """A layer whose weights are stored past the caches, merged in one launch (128-column tiles at rank 8) and projection by
+    projection (64-column tiles): the same bits, and sampled rows as the oracle's.  d_ffn ends inside a tile of either."""
+    cfg = inputs.TINY.replace(name="wide", n_layers=1, d_model=2560, n_heads=20, d_ffn=6792, batch=1)
+    S = Setup(cfg, seed=5, max_batch=1)
+    ad = inputs.make_lora(cfg, rank, seed=5, device="cuda")
+    _merge_all(S, ad, SCALE, [0])
+    sep = {w: _read_packed(S.model, cfg, w, 0).clone() for w in (5, 6, 7, 8)}
+    S.model.lora_merge_layer(0, S.w["layers"][0], {k: (a, torch.zeros_like(b)) for k, (a, b) in ad[0].items()}, SCALE)
+    S.model.lora_merge_layer(0, S.w["layers"][0], ad[0], SCALE)
+    adc = {k: (a.cpu(), b.cpu()) for k, (a, b) in ad[0].items()}
+    for w in (5, 6, 7, 8):
+        buf = _read_packed(S.model, cfg, w, 0)
+        _assert_same_packed(cfg, w, buf, sep[w], f"rank {rank}")
+        R, _ = _packed_shape(cfg, w)
+        _check_packed(cfg, buf, w, [0, 31, 32, 63, 64, R // 3, R // 2 + 1, R - 65, R - 1], S.wc["layers"][0], adc, SCALE,
+                      f"d 2560 r{rank} w{w}")
+    S.model.close()
+
+
 def test_lora_merge_starts_from_the_original_and_a_zero_update_restores(tiny):
     S, cfg = tiny, inputs.TINY
     packed0 = {w: _read_packed(S.model, cfg, w, 0).clone() for w in (5, 6, 7, 8)}
