@@ -261,7 +261,7 @@ __global__ void bf16_to_f32_kernel(float* dst, const bf16_t* src, int n) {
 }
 
 // dst = src, 4 x 16 bytes per thread; the stores bypass the caches (404 MB: 5.0 -> 5.6 TB/s, the runtime's copy
-// before).
+// before; smaller copies: launch_copy).  Only vla_debug_read copies so.
 __global__ __launch_bounds__(256) void copy_kernel(const u32x4* __restrict__ src, u32x4* __restrict__ dst, size_t n16) {
   const size_t i0 = (size_t)blockIdx.x * 1024 + threadIdx.x;
   u32x4 v[4];
@@ -576,7 +576,11 @@ hipError_t launch_gather_rows(const float* x, const bf16_t* o, const int32_t* ro
 
 hipError_t launch_copy(void* dst, const void* src, size_t bytes, hipStream_t s) {
   if (bytes == 0) return hipSuccess;
-  if (((uintptr_t)dst | (uintptr_t)src | bytes) % 16 != 0) return hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToDevice, s);
+  // The runtime's copy below 8 MB: it writes through the caches (0.1 to 2 MB 2.0-2.2 us, copy_kernel 3.6-4.4).  The four
+  // packed weights of a layer read back, runtime / kernel: d = 1536 (4.7 to 26 MB) 26.9 / 27.2 us, d = 2560 (13 to 71 MB)
+  // 69 / 50, d = 4096 (34 to 182 MB) 157 / 144.
+  if (bytes < (8u << 20) || ((uintptr_t)dst | (uintptr_t)src | bytes) % 16 != 0)
+    return hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToDevice, s);
   const size_t n16 = bytes / 16;
   hipLaunchKernelGGL(copy_kernel, dim3((unsigned)((n16 + 1023) / 1024)), dim3(256), 0, s, static_cast<const u32x4*>(src),
                      static_cast<u32x4*>(dst), n16);

@@ -215,6 +215,22 @@ def test_lora_merge_layer_gives_the_bits_of_the_separate_merges(tiny):
         _assert_same_packed(cfg, w, _read_packed(S.model, cfg, w, 1), before[w], "a zero update restores the layer")
 
 
+def test_weights_read_back_in_part():
+    """Reads on either side of the size from which a kernel copies, of whole and of odd numbers of 16 bytes, and into an
+    unaligned buffer hold the first bytes of the whole read, and nothing past them is written."""
+    cfg = inputs.TINY.replace(name="read", n_layers=1, d_model=1024, n_heads=8, d_ffn=2752, batch=1)
+    S = Setup(cfg, seed=6, max_batch=1)
+    whole = _read_packed(S.model, cfg, 7, 0)
+    edge = (8 << 20) // 2
+    for n in (1, 8, 12345, edge - 8, edge, edge + 1, edge + 8 * 1024 + 8, whole.numel()):
+        for skip in (0, 1):
+            buf = torch.full((skip + n + 8,), 7.0, dtype=torch.bfloat16, device="cuda")
+            S.model.debug_read(7, 0, buf[skip:skip + n])
+            assert _same_bits(buf[skip:skip + n], whole[:n]), (n, skip)
+            assert bool((buf[skip + n:] == 7.0).all()) and bool((buf[:skip] == 7.0).all()), (n, skip)
+    S.model.close()
+
+
 @pytest.mark.parametrize("rank", [8, 64])
 def test_lora_merge_tile_widths_give_the_same_bits(rank):
     """A layer whose weights are stored past the caches, merged in one launch (128-column tiles at rank 8) and projection by
