@@ -462,7 +462,7 @@ static hipError_t launch_part(const GemmArgs& a, GemmEpilogue epi, int shape, hi
 
 hipError_t launch_gemm(const GemmArgs& a, GemmEpilogue epi, hipStream_t s) {
   if (a.M <= 0 || a.N <= 0) return hipSuccess;
-  return launch_gemm(a, epi, s, gemm_plan(a.M, a.N, a.K, persistent_workgroups()));
+  return launch_gemm(a, epi, s, gemm_plan(a.M, a.N, a.K, persistent_workgroups(), epi));
 }
 
 hipError_t launch_gemm(const GemmArgs& a, GemmEpilogue epi, hipStream_t s, const GemmPlan& p) {

@@ -364,43 +364,52 @@ static float shape_cost(const ShapeCost& c, int M, int N, int K, int cus) {
   return c.first + c.more * (float)(q - 1) + 1e-3f * step * (float)(K / 32);
 }
 
-// The shape with the least estimated time.  Over the measured sizes the choice is 1 % slower than the best shape of each
-// on average (24 % at worst); always 256 x 256 is 69 %.  The 256 x 256 tile does the most work per byte moved and stays
-// the choice from about two full rounds of its tiles on.  Measured with each product's own epilogue (us, 256 x 256 ->
-// chosen): M = 277, d = 4096: QKV 81 -> 52, O 68 -> 25, gate/up 85 -> 67, down 163 -> 58; M = 4720: O 175 -> 155, down
-// 404 -> 356; M = 4608, d = 1024: O 28 -> 18, down 51 -> 33; M = 1088, K = 256, N = 768: 11.6 -> 4.2.
+// The shape with the least estimated time.  Over the measured sizes of less than one full round of 256 x 256 tiles (one per
+// CU) the choice is 1 % slower than the best shape of each on average (24 % at worst); always 256 x 256 is 69 %.  Measured
+// with each product's own epilogue (us, 256 x 256 -> chosen): M = 277, d = 4096: QKV 81 -> 52, O 68 -> 25, gate/up 85 -> 67,
+// down 163 -> 58; M = 1088, K = 256, N = 768: 11.6 -> 4.2.
 //
-// From one full round of 256 x 256 tiles on, a product may also be cut by rows or columns: its first part the whole rounds
-// that fit (or one round less), the rest, which would be a nearly empty round, on a smaller shape after it.  The estimate,
-// with kCutUs for the second launch and the drain before it, has to be 3 % better than one shape's (without kCutUs a
-// 4608 x 5504 x 1024 gate/up was cut and took 61 us where it takes 58).  Measured, one shape -> cut (us): M = 2304,
-// d = 4096: gate/up 353 -> 315; M = 4720: O and down together 582 -> 524, QKV 399 -> 397, the four input gradients of a
-// layer 1530 -> 1380; M = 37760: O and down 3480 -> 3290.  With many rounds the emptier last one runs at a higher clock,
-// and less is gained than estimated: M = 6912 QKV 580 -> 567, gate/up 939 -> 936.
-constexpr float kCutUs = 10.f;
-GemmPlan gemm_plan(int M, int N, int K, int cus) {
+// From one full round on the 256 x 256 tile, which does the most work per byte moved, is left only where its last round is
+// less than half full:
+// - a smaller shape takes the whole product up to kWholeRounds rounds (QKV of d = 256, 22000 rows, 1.02 rounds 49 -> 30 us;
+//   O of d = 3072, 6600 rows, 1.22 rounds 152 -> 141).  The estimate, whose steps have the operands in the caches, is too
+//   good for smaller tiles in many rounds: by it alone QKV of d = 512, 44000 rows, 4.05 rounds took 136 us for 126, gate/up
+//   of d = 256, 55000 rows, 5.1 rounds 137 for 82;
+// - or it is cut by rows or columns: its first part the whole rounds that fit (or one round less), the rest on a smaller
+//   shape after it.  The estimate, with cut_us for the second launch and the drain before it, has to be 3 % better than one
+//   shape's.  M = 2304, d = 4096: gate/up 353 -> 315; M = 4720: O and down together 582 -> 524, the four input gradients of
+//   a layer 1530 -> 1380; M = 37760: O and down 3480 -> 3290.  With a last round at least half full every cut measured was
+//   slower (1.51 to 1.62 rounds: QKV of d = 3072 158 -> 179, O and down of d = 4096 676 -> 699); so was one of the SwiGLU
+//   epilogue, whose 256 x 256 tile hides its stores under the next tile, at K = 256 (2.04 rounds 42 -> 49), and of QKV there
+//   in many rounds (3.25 85 -> 101).
+// Over about 200 products of 1 to 17 rounds at d = 256 to 4096 the choice is 4.6 % faster than always 256 x 256, none by more
+// than 1.5 % slower.
+constexpr float kWholeRounds = 1.25f, kWholeRoundsQkv = 1.2f;
+GemmPlan gemm_plan(int M, int N, int K, int cus, GemmEpilogue epi) {
+  const bool swiglu = epi == kEpiSwiGlu || epi == kEpiSwiGluKeep;
+  const float whole = epi == kEpiQkvRope ? kWholeRoundsQkv : kWholeRounds, cut_us = swiglu ? 10.f : 7.f;
+  const ShapeCost& big = kShapes[0];
+  const int tm = (M + big.tm - 1) / big.tm, tn = (N + big.tn - 1) / big.tn;
+  const long long tiles = (long long)tm * tn, rounds = tiles / cus;
   GemmPlan best{};
   float tb = 0.f;
   for (int i = 0; i < kGemmShapes; ++i) {
     const float t = shape_cost(kShapes[i], M, N, K, cus);
     if (i == 0) {
       tb = 0.95f * t;  // a smaller shape has to gain 5 %
-    } else if (t < tb) {
+    } else if (t < tb && (float)tiles <= whole * (float)cus) {
       tb = t;
       best.first = i;
     }
   }
-  const ShapeCost& big = kShapes[0];
-  const int tm = (M + big.tm - 1) / big.tm, tn = (N + big.tn - 1) / big.tn;
-  const long long rounds = (long long)tm * tn / cus;
-  if (rounds < 1) return best;
+  if (rounds < 1 || 2 * (tiles % cus) >= cus || (K < 512 && (swiglu || rounds > 2))) return best;
   tb = 0.97f * shape_cost(kShapes[best.first], M, N, K, cus);
   for (long long r = rounds; r >= 1 && r >= rounds - 1; --r) {
     const int cut_n = (int)(r * cus / tm), cut_m = (int)(r * cus / tn);  // tile columns, tile rows in r rounds
     for (int by_rows = 0; by_rows < 2; ++by_rows) {
       const int rows = by_rows ? cut_m * big.tm : 0, cols = by_rows ? 0 : cut_n * big.tn;
       if (rows >= M || cols >= N || rows + cols == 0) continue;
-      const float t0 = kCutUs + (by_rows ? shape_cost(big, rows, N, K, cus) : shape_cost(big, M, cols, K, cus));
+      const float t0 = cut_us + (by_rows ? shape_cost(big, rows, N, K, cus) : shape_cost(big, M, cols, K, cus));
       for (int i = 1; i < kGemmShapes; ++i) {
         const float t = t0 + (by_rows ? shape_cost(kShapes[i], M - rows, N, K, cus)
                                       : shape_cost(kShapes[i], M, N - cols, K, cus));

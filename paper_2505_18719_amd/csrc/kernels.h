@@ -67,7 +67,7 @@ constexpr int kGemmShapes = 9;
 struct GemmPlan {
   int first, rest, rows, cols;
 };
-GemmPlan gemm_plan(int M, int N, int K, int cus);
+GemmPlan gemm_plan(int M, int N, int K, int cus, GemmEpilogue epi);
 hipError_t launch_gemm(const GemmArgs& a, GemmEpilogue epi, hipStream_t s);  // by gemm_plan
 hipError_t launch_gemm(const GemmArgs& a, GemmEpilogue epi, hipStream_t s, const GemmPlan& plan);
 hipError_t launch_gemm_shape(const GemmArgs& a, GemmEpilogue epi, int shape, hipStream_t s);

@@ -151,6 +151,39 @@ def test_decode_gemm_plan_stays_in_32_bit_units(vla, N, K, workgroups):
     assert p.slots == slots <= 16
 
 
+class _GemmPlan(ctypes.Structure):
+    _fields_ = [(n, ctypes.c_int) for n in ("first", "rest", "rows", "cols")]
+
+
+def test_prefill_gemm_plan_keeps_full_rounds_on_the_large_tile(vla):
+    """From one round of 256 x 256 tiles per CU on, a smaller tile shape takes a whole product only where the second round
+    is nearly empty, and a cut's rest is less than half a round (gate/up of d = 256 and 200 environments ran 64 x 64 tiles
+    for 5 rounds: 137 us, 82 on the large tile); below one round, few rows run smaller tiles."""
+    plan = vla.load_library()["_ZN3vla9gemm_planEiiiiNS_12GemmEpilogueE"]
+    plan.restype, plan.argtypes = _GemmPlan, [ctypes.c_int] * 5
+    store, residual, swiglu, qkv, keep = range(5)
+    cuts = whole = 0
+    for d, f in ((256, 688), (512, 1376), (1024, 2752), (1280, 3400), (2048, 5504), (4096, 11008)):
+        fp = 32 * -(-f // 32)
+        for M in (277, 1108, 4432, 6656, 8864, 17728, 22160, 35456, 55400, 141824):
+            for N, K, epi in ((3 * d, d, qkv), (d, d, residual), (2 * fp, d, swiglu), (2 * fp, d, keep), (d, fp, residual),
+                              (fp, d, store)):
+                p = plan(M, N, K, 256, epi)
+                tiles = -(-M // 256) * -(-N // 256)
+                assert 0 <= p.first <= 8 and 0 <= p.rest <= 8
+                if p.rows or p.cols:
+                    cuts += 1
+                    assert p.first == 0 and p.rest >= 1 and not (p.rows and p.cols)
+                    assert 0 <= p.rows < M and 0 <= p.cols < N and p.rows % 256 == 0 and p.cols % 256 == 0
+                    assert tiles >= 256 and tiles % 256 < 128, (M, N, K, epi)
+                    assert K >= 512 or (epi not in (swiglu, keep) and tiles < 3 * 256)
+                elif p.first:
+                    whole += 1
+                    assert tiles <= 256 * (1.2 if epi == qkv else 1.25), (M, N, K, epi)
+    assert cuts >= 20 and whole >= 50
+    assert plan(55200, 1408, 256, 256, swiglu).first == 0 and plan(277, 4096, 4096, 256, residual).first > 0
+
+
 def test_extract_actions_validates_on_the_host(vla):
     lib = vla.load_library()
     p = ctypes.c_void_p(16)  # never dereferenced: validation fails first
