@@ -86,29 +86,37 @@ __global__ __launch_bounds__(64 * kGaeChunks) void gae_kernel(GaeArgs a) {
 }
 
 // The surrogate of action t: its term and clip flag are added to (surr, clip), its token gradient is returned.  The
-// token loads are unrolled to the largest n_tokens, so that they are in flight together.
+// token loads are unrolled to MAX >= n_tokens, so that they are in flight together (0: a plain loop, for one or two tokens).
 constexpr int kPpoMaxTokens = 16;
+template <int MAX>
 __device__ __forceinline__ float ppo_action(const PpoArgs& a, int t, float& surr, float& clip) {
   const float* ln = a.logp_new + (size_t)t * a.n_tokens;
   const float* lo = a.logp_old + (size_t)t * a.n_tokens;
-  float vn[kPpoMaxTokens], vo[kPpoMaxTokens];
   const float A = a.advantages[t];
-#pragma unroll
-  for (int i = 0; i < kPpoMaxTokens; ++i)
-    if (i < a.n_tokens) {
-      vn[i] = ln[i];
-      vo[i] = lo[i];
-    }
   float sn = 0.f, so = 0.f;
-#pragma unroll
-  for (int i = 0; i < kPpoMaxTokens; ++i)
-    if (i < a.n_tokens) {
-      sn += vn[i];
-      so += vo[i];
+  if constexpr (MAX == 0) {
+    for (int i = 0; i < a.n_tokens; ++i) {
+      sn += ln[i];
+      so += lo[i];
     }
+  } else {
+    float vn[MAX], vo[MAX];
+#pragma unroll
+    for (int i = 0; i < MAX; ++i)
+      if (i < a.n_tokens) {
+        vn[i] = ln[i];
+        vo[i] = lo[i];
+      }
+#pragma unroll
+    for (int i = 0; i < MAX; ++i)
+      if (i < a.n_tokens) {
+        sn += vn[i];
+        so += vo[i];
+      }
+  }
   const float rho = expf(sn - so);
   const float rc = fminf(fmaxf(rho, 1.f - a.eps), 1.f + a.eps);
-  const bool clipped = (A > 0.f && rho > 1.f + a.eps) || (A < 0.f && rho < 1.f - a.eps);
+  const bool clipped = ((A > 0.f) & (rho > 1.f + a.eps)) | ((A < 0.f) & (rho < 1.f - a.eps));  // no branches
   surr += fminf(rho * A, rc * A);
   clip += clipped ? 1.f : 0.f;
   return clipped ? 0.f : -rho * A / (float)a.n;
@@ -136,10 +144,11 @@ __device__ __forceinline__ void ppo_block_sum(float& surr, float& clip) {
 // ... in order, the partial sums are combined by fixed wave and LDS trees, so
 // the loss is the same bits on every run.
 constexpr int kPpoThreads = 1024;
+template <int MAX>
 __global__ __launch_bounds__(kPpoThreads) void ppo_clip_kernel(PpoArgs a) {
   float surr = 0.f, clip = 0.f;
   for (int t = threadIdx.x; t < a.n; t += kPpoThreads) {
-    const float g = ppo_action(a, t, surr, clip);
+    const float g = ppo_action<MAX>(a, t, surr, clip);
     float* dl = a.dlogp + (size_t)t * a.n_tokens;
     for (int i = 0; i < a.n_tokens; ++i) dl[i] = g;
   }
@@ -157,10 +166,10 @@ __global__ __launch_bounds__(kPpoThreads) void ppo_clip_kernel(PpoArgs a) {
 // inputs are read by its own thread before any of its gradients is written, as in the one-workgroup kernel.
 constexpr int kPpoSplitThreads = 256;
 __global__ __launch_bounds__(kPpoSplitThreads) void ppo_split_kernel(PpoArgs a, int per) {
-  const int t0 = blockIdx.x * per, t1 = min(a.n, t0 + per), tid = threadIdx.x;
+  const int t0 = blockIdx.x * per, t1 = t0 + min(per, a.n - t0), tid = threadIdx.x;
   float surr = 0.f, clip = 0.f, g0 = 0.f;
   for (int t = t0 + tid; t < t1; t += kPpoSplitThreads) {
-    const float g = ppo_action(a, t, surr, clip);
+    const float g = ppo_action<kPpoMaxTokens>(a, t, surr, clip);
     if (t == t0) {
       g0 = g;
       continue;
@@ -177,6 +186,7 @@ __global__ __launch_bounds__(kPpoSplitThreads) void ppo_split_kernel(PpoArgs a, 
   }
 }
 
+constexpr long long kPpoSplitWork = 160 << 10;  // actions x tokens x (tokens + 1)
 constexpr int kPpoMaxSplit = 1024;  // workgroups of ppo_split_kernel: one thread of ppo_finish_kernel each
 __global__ __launch_bounds__(kPpoMaxSplit) void ppo_finish_kernel(PpoArgs a, int per, int groups) {
   const int b = threadIdx.x;
@@ -285,12 +295,21 @@ hipError_t launch_gae(const GaeArgs& a, hipStream_t s) {
 
 hipError_t launch_ppo_clip(const PpoArgs& a, hipStream_t s) {
   if (a.n <= 0) return hipErrorInvalidValue;
-  // One workgroup while it makes one pass (a second launch costs 3 us, each further pass about 5); and below 3 tokens, where an
-  // action's gradients have no room for a workgroup's sums.
-  if (a.n <= kPpoThreads || a.n_tokens < 3) {
-    hipLaunchKernelGGL(ppo_clip_kernel, dim3(1), dim3(kPpoThreads), 0, s, a);
+  // One workgroup where that takes less than the second launch costs: its time goes with the actions and about the square
+  // of their tokens (strided loads), and it meets the 12 us of a call of two launches at 3000 actions of 7 tokens (13.5 / 11.9
+  // us a call), 9000 of 3 (11.6 / 12), 600 of 16 (13.7 / 12); 4096 of 7 17.7 / 12.1, 2048 of 7 9.8 / 11.9; 8 tokens take
+  // twice as long as the others would have it (2048 actions 21 us).  And below 3 tokens, where an action's gradients have no
+  // room for a workgroup's sums.  The loads are unrolled to little more than the tokens: 20000 actions of one token take 10.0
+  // us, with 16 loads unrolled 19.5.
+  const long long work = (long long)a.n * a.n_tokens * (a.n_tokens + 1) * (a.n_tokens == 8 ? 2 : 1);
+  if (a.n_tokens < 3 || work < kPpoSplitWork) {
+    const dim3 block(kPpoThreads);
+    if (a.n_tokens <= 2) hipLaunchKernelGGL(ppo_clip_kernel<0>, dim3(1), block, 0, s, a);
+    else if (a.n_tokens <= 4) hipLaunchKernelGGL(ppo_clip_kernel<4>, dim3(1), block, 0, s, a);
+    else if (a.n_tokens <= 8) hipLaunchKernelGGL(ppo_clip_kernel<8>, dim3(1), block, 0, s, a);
+    else hipLaunchKernelGGL(ppo_clip_kernel<kPpoMaxTokens>, dim3(1), block, 0, s, a);
   } else {
-    const int per = std::max(kPpoSplitThreads, (a.n + kPpoMaxSplit - 1) / kPpoMaxSplit), groups = (a.n + per - 1) / per;
+    const int per = std::max(kPpoSplitThreads, (a.n - 1) / kPpoMaxSplit + 1), groups = (a.n - 1) / per + 1;
     hipLaunchKernelGGL(ppo_split_kernel, dim3(groups), dim3(kPpoSplitThreads), 0, s, a, per);
     hipLaunchKernelGGL(ppo_finish_kernel, dim3(1), dim3(kPpoMaxSplit), 0, s, a, per, groups);
   }

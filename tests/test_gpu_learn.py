@@ -111,10 +111,13 @@ def test_ppo_clip_matches_oracle(n, k, spread):
     _ppo_check(n, k, 0.2, seed=n + k, spread=spread, adv_zero_frac=0.01)
 
 
-@pytest.mark.parametrize("n,k", [(1024, 7), (1025, 7), (1280, 3), (1281, 4), (2000, 2), (262145, 3), (300000, 16)])
+@pytest.mark.parametrize("n,k", [(1024, 7), (1025, 7), (1280, 3), (1281, 4), (2000, 2), (262145, 3), (300000, 16),
+                                 (2925, 7), (2926, 7), (13653, 3), (13824, 3), (602, 16), (603, 16), (8192, 4), (20001, 1),
+                                 (5000, 5), (20001, 2), (1137, 8), (1138, 8)])
 def test_ppo_clip_over_many_workgroups(n, k):
-    """Either side of one workgroup's range, whole and nearly empty last workgroups, too few tokens to split, more
-    actions than 1024 workgroups of 256; and gradients written over the new log-probs."""
+    """Either side of where one workgroup takes all (163840 actions x tokens x (tokens + 1), half of that for 8 tokens), every unrolling of its token
+    loads, whole and nearly empty last workgroups, too few tokens to split, more actions than 1024 workgroups of 256; and
+    gradients written over the new log-probs."""
     _, g = _ppo_check(n, k, 0.2, seed=n + k, spread=0.05, adv_zero_frac=0.01)
     old, new, adv = [torch.from_numpy(x).cuda() for x in inputs.ppo_minibatch(n, k, seed=n + k, spread=0.05)]
     adv[: int(n * 0.01)] = 0.0
