@@ -15,26 +15,24 @@ namespace {
 constexpr int kGaeChunks = 16;  // waves per workgroup; each takes one slice of the time axis
 
 // Steps t1 - 1 .. t0 of environment n, last first: step(t, delta_t, gamma lam (1 - d_{t+1}), V_t).  The recursion is
-// serial but its inputs are not, so kGaeAhead steps' loads go out together (a window has few waves to cover a load's
-// latency: 256 environments are 4 workgroups, 15.0 -> 10.2 us at 256 x 256).
-constexpr int kGaeAhead = 8;
-template <class F>
+// serial but its inputs are not, so AHEAD steps' loads go out together (a window has few waves to cover a load's latency).
+template <int AHEAD, class F>
 __device__ __forceinline__ void gae_steps(const GaeArgs& a, int n, int t0, int t1, F step) {
   const size_t N = a.n_env;
   const float gl = a.gamma * a.lam;
   float vn = a.values[t1 * N + n];
-  for (int t = t1 - 1; t >= t0; t -= kGaeAhead) {
-    float r[kGaeAhead], v[kGaeAhead];
-    uint8_t d[kGaeAhead];
+  for (int t = t1 - 1; t >= t0; t -= AHEAD) {
+    float r[AHEAD], v[AHEAD];
+    uint8_t d[AHEAD];
 #pragma unroll
-    for (int u = 0; u < kGaeAhead; ++u)
+    for (int u = 0; u < AHEAD; ++u)
       if (t - u >= t0) {
         r[u] = a.rewards[(t - u) * N + n];
         v[u] = a.values[(t - u) * N + n];
         d[u] = a.dones[(t - u + 1) * N + n];
       }
 #pragma unroll
-    for (int u = 0; u < kGaeAhead; ++u)
+    for (int u = 0; u < AHEAD; ++u)
       if (t - u >= t0) {
         const float c = d[u] ? 0.f : 1.f;
         step(t - u, r[u] + a.gamma * c * vn - v[u], gl * c, v[u]);
@@ -50,6 +48,7 @@ __device__ __forceinline__ void gae_steps(const GaeArgs& a, int n, int t0, int t
 // slice maps are chained backwards from A_M = 0 in LDS, and pass 2 replays
 // each slice from its true incoming advantage, writing A_t and A_t + V_t.
 // Every wave reads rows t of 64 consecutive environments (coalesced).
+template <int AHEAD>
 __global__ __launch_bounds__(64 * kGaeChunks) void gae_kernel(GaeArgs a) {
   __shared__ float P[kGaeChunks][64], Q[kGaeChunks][64], Ain[kGaeChunks][64];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -60,7 +59,7 @@ __global__ __launch_bounds__(64 * kGaeChunks) void gae_kernel(GaeArgs a) {
   const bool live = n < N;
   float p = 0.f, q = 1.f;
   if (live) {
-    gae_steps(a, n, t0, t1, [&](int, float delta, float kc, float) {
+    gae_steps<AHEAD>(a, n, t0, t1, [&](int, float delta, float kc, float) {
       p = delta + kc * p;
       q = kc * q;
     });
@@ -78,7 +77,7 @@ __global__ __launch_bounds__(64 * kGaeChunks) void gae_kernel(GaeArgs a) {
   __syncthreads();
   if (!live) return;
   float adv = Ain[w][lane];
-  gae_steps(a, n, t0, t1, [&](int t, float delta, float kc, float v) {
+  gae_steps<AHEAD>(a, n, t0, t1, [&](int t, float delta, float kc, float v) {
     adv = delta + kc * adv;
     a.advantages[(size_t)t * N + n] = adv;
     if (a.returns) a.returns[(size_t)t * N + n] = adv + v;
@@ -289,7 +288,13 @@ __global__ __launch_bounds__(256) void logprob_backward4_kernel(LogprobBwdArgs a
 
 hipError_t launch_gae(const GaeArgs& a, hipStream_t s) {
   if (a.n_env <= 0 || a.n_steps <= 0) return hipSuccess;
-  hipLaunchKernelGGL(gae_kernel, dim3((a.n_env + 63) / 64), dim3(64 * kGaeChunks), 0, s, a);
+  const dim3 grid((a.n_env + 63) / 64), block(64 * kGaeChunks);
+  // Eight steps' loads together where a slice has more than four steps and the rows of its steps are not in one cache line
+  // (inputs not in the caches, us, one by one / eight: 64 x 512 26.6 / 16.0, 256 x 256 14.6 / 10.0, 16 x 512 24.6 / 15.1;
+  // in the caches 4096 x 512 22.5 / 16.6, 64 x 512 13.7 / 13.7).  Otherwise the loads that a window has no steps for only
+  // cost (in the caches 64 x 16 2.1 / 2.7, 64 x 64 3.4 / 3.6; one environment, 512 steps, 15.6 / 16.9).
+  if (a.n_steps > 4 * kGaeChunks && a.n_env >= 16) hipLaunchKernelGGL(gae_kernel<8>, grid, block, 0, s, a);
+  else hipLaunchKernelGGL(gae_kernel<1>, grid, block, 0, s, a);
   return hipGetLastError();
 }
 

@@ -39,8 +39,11 @@ def _run_gae(N, M, gamma, lam, seed=0, p_done=0.01, returns=True):
     return r, v, d, adv.cpu().numpy(), ret.cpu().numpy(), a_ref, ret_ref
 
 
+# one step and eight steps of loads at a time: on either side of 64 steps and 16 environments too, with whole and partial
+# batches in a slice
 @pytest.mark.parametrize("N,M,p_done", [(64, 512, 0.01), (70, 37, 0.2), (3, 1, 0.0), (130, 5, 0.3),
-                                        (4096, 128, 0.02)])
+                                        (4096, 128, 0.02), (64, 64, 0.05), (64, 65, 0.05), (15, 300, 0.02), (16, 300, 0.02),
+                                        (17, 129, 0.1)])
 def test_gae_matches_oracle(N, M, p_done):
     gamma, lam = 0.99, 0.95
     r, v, d, adv, ret, a_ref, ret_ref = _run_gae(N, M, gamma, lam, seed=N + M, p_done=p_done)
