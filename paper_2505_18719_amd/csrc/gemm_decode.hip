@@ -65,8 +65,8 @@ hipError_t launch_rows(const SkinnyArgs& a, const SkinnyPlan& p, hipStream_t st)
   const int mb = (a.M + 15) / 16;
   if (mb <= 1) return launch_mb<1, T, S>(a, p, st);
   if (mb <= 2) return launch_mb<2, T, S>(a, p, st);
-  if (mb <= 4) return launch_mb<4, T, S>(a, p, st);
-  return launch_mb<8, T, S>(a, p, st);
+  if (S || mb <= 4) return launch_mb<4, T, S>(a, p, st);  // S: at most 64 rows
+  if constexpr (!S) return launch_mb<8, T, S>(a, p, st);
 }
 
 }  // namespace
@@ -87,11 +87,18 @@ SkinnyPlan skinny_plan(int N, int K, int workgroups, int max_slots) {
   return p;
 }
 
+constexpr long long kStreamElems = 24 << 20;
 hipError_t launch_skinny(const SkinnyArgs& a, const SkinnyPlan& p, hipStream_t st) {
   if (a.M <= 0 || a.N <= 0) return hipSuccess;
   if (a.M > 128 || !skinny_plan_ok(p, a.N, a.K) || (long long)frag_elems(a.N, a.K) * 2 >= (1ll << 31))
     return hipErrorInvalidValue;
-  return a.stream ? launch_rows<false, true>(a, p, st) : launch_rows<false, false>(a, p, st);
+  // Past the caches where the model asks for it (its weights do not fit the last-level cache), from 48 MB a product on and up
+  // to 64 rows.  One product, us, one row, through the caches / past them: 180 MB 33.7 / 31.5, 104 MB 20.2 / 19.3, 52 MB
+  // 12.2 / 11.7, 46 MB 10.6 / 10.8, 34 MB 8.7 / 8.6, 19 MB 6.6 / 7.1, 12 MB 5.4 / 5.7.  All products of a decode with every one
+  // past the caches: d = 4096, eight layers, 1 / 64 / 128 rows 3800 -> 3612, 5219 -> 5055, 6878 -> 6861; but d = 2048, eight
+  // layers 1484 -> 1556, 2425 -> 2489, 3319 -> 3547; d = 1024, 16 layers 1775 -> 1889, 3175 -> 3403, 4979 -> 5205.
+  const bool stream = a.stream && a.M <= 64 && (long long)a.N * a.K >= kStreamElems;
+  return stream ? launch_rows<false, true>(a, p, st) : launch_rows<false, false>(a, p, st);
 }
 
 // C = A W with W [kt, ldw] as it lies (the gradients' products over the rows of an activation matrix): the same units, slots

@@ -89,7 +89,7 @@ struct SkinnyArgs {
   // launch_skinny_t: W holds the contraction along its rows, [kt, ldw] in frag layout with the N columns from col0 on
   // (col0 % 32 == 0); rows from kt up to K count as zeros, whatever W's last row block holds there
   int kt, ldw, col0;
-  bool stream;  // launch_skinny: the weights are read past the caches
+  bool stream;  // launch_skinny: large weights are read past the caches
 };
 struct SkinnyPlan {
   int tiles;     // N / 64

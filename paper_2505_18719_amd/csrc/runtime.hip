@@ -162,7 +162,7 @@ struct vla_model {
   // decode GEMM work splits (one persistent workgroup per CU)
   SkinnyPlan plan_qkv, plan_o, plan_gu, plan_d, plan_head;
   int cus;  // compute units: the skinny GEMM's persistent grid
-  bool stream_w;      // decode reads the layers' weights past the caches
+  bool stream_w;      // decode reads the larger of the layers' weights past the caches (launch_skinny)
   bool stream_merge;  // merges store them past the caches
   // persistent decode layer kernel: its buffers, and whether the device runs it
   float *part_o, *part_gu, *part_dn, *part_nx;  // split-K partials of each projection of a layer launch
@@ -778,10 +778,10 @@ int vla_create(const vla_config* cfg, const vla_weights* w, void* workspace, siz
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
       cus = 256;
     m->cus = cus;
-    // A decode step reads every layer's weights once.  Where they do not fit the 256 MB last-level cache, keeping them there
-    // only displaces what is read again (7B width, four layers, one environment: decode 2545 -> 2425 us; eight layers, 64
-    // environments 8900 -> 8855); where they fit (mid preset, 200 MB) the next step finds them (1930 us, past the caches
-    // 1996).
+    // A decode step reads every layer's weights once.  Where they do not fit the 256 MB last-level cache, keeping the large
+    // ones there only displaces what is read again (7B width, four layers, one environment: decode 2545 -> 2425 us; eight
+    // layers, 64 environments 8900 -> 8855); where they fit (mid preset, 200 MB) the next step finds them (1930 us, past the
+    // caches 1996).  Which products: launch_skinny.
     const size_t layers = D.L * (frag_elems(4 * D.d, D.d) + frag_elems(2 * D.Fp, D.d) + frag_elems(D.d, D.Fp)) * sizeof(bf16_t);
     m->stream_w = layers > (size_t)256 << 20;
     // A merge of every layer reads as much again, the original weights: where both do not fit that cache, what is merged
