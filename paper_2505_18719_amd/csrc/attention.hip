@@ -326,6 +326,8 @@ __global__ __launch_bounds__(256) void attn_decode_kernel(DecodeAttnArgs a) {
   const int key0 = tid / LPK, part = tid % LPK;
   const int i = tid % HD, grp = __builtin_amdgcn_readfirstlane(tid / HD);
   auto k_row = [&](int it) {  // this lane's 8 features of key KPP it + key0
+    // with many workgroups memory bounds it, and the keys past the sequence in its last page are not read
+    if (KP == 0 && KPP * it + key0 >= pos) return make_uint4(0, 0, 0, 0);
     const int page = pt[min(KPP / kPage * it + wave * (64 / LPK) / kPage, last)];
     return *reinterpret_cast<const uint4*>(a.kv.k + (((size_t)page * H + head) * kPage + key0 % kPage) * HD + part * 8);
   };
@@ -589,7 +591,8 @@ hipError_t launch_attn_decode(const DecodeAttnArgs& a, hipStream_t s) {
   if (a.head_dim != 128 && a.head_dim != 64) return hipErrorInvalidValue;
   // By workgroups per CU, which is what covers a workgroup's waits (us, all of a sequence ahead / 4 passes and 2 pages
   // at a time / one by one; a workgroup that looked up its pages in LDS and read one by one before): head_dim 128, at
-  // most one per CU 11.1 / 14.9 / 19.9 (28.0), 2 22.2 / 19.7 / 25.6, 4 42.4 / 32.7 / 34.6, 8 75 / 69.7 / 60.7 (59.0);
+  // most one per CU 11.1 / 14.9 / 19.9 (28.0), 2 22.2 / 19.7 / 25.6, 4 42.4 / 32.7 / 34.6, 8 75 / 69.7 / 60.7 (59.0), and
+  // without the last page's keys past the sequence 58.6 (58.5), 12 91.8 (94.2), 14 104.6 (105.2), 16 124.7 (122);
   // head_dim 64, one 8.9 / 10.9 / 11.8 (19.2), 4 19.7 / 17.5 / 17.2, 8 41.9 / 37.4 / 32.7.
   const long long wgs = (long long)a.B * a.n_heads;
   const bool few = wgs <= a.cus, some = wgs <= 4ll * a.cus;
