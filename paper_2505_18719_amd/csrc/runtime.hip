@@ -686,7 +686,7 @@ int layer_backward(vla_model* m, TrainBufs& t, int l, int B, int M, const vla_lo
     for (int b0 = 0; b0 < n; b0 += per) {
       LoraGroup lg{std::min(per, n - b0), r16, {}};
       const int rows = lg.n * r16;
-      int col0 = ps[b0].o0, col1 = 0;  // the columns of dY that these projections use
+      int col0 = ps[b0].o0, col1 = 0;  // the columns of dY from the first of these projections to the last
       for (int i = 0; i < lg.n; ++i) {
         const Proj& q = ps[b0 + i];
         lg.p[i] = LoraGradArgs{q.o0, q.n_cols, in, q.out, q.mode, D.hd, q.part,
@@ -701,7 +701,8 @@ int layer_backward(vla_model* m, TrainBufs& t, int l, int B, int M, const vla_lo
       if ((e = launch_reduce_frag(t.spart, sp, rows, M, Mk, t.t1f, s)) != hipSuccess) return e;
       if ((e = skinny_to(t.bpt, rows, dY, Mp, ky)) != hipSuccess) return e;
       if ((e = launch_reduce_frag(t.spart, sp, rows, M, Mk, t.t2f, s)) != hipSuccess) return e;
-      // dB of all projections from one pass over their columns of dY
+      // dB of all projections from one pass over those columns (without an adapter on k, its columns between q's and v's
+      // are multiplied too, and not used)
       if ((e = skinny_rows(t.t1f, rows, dY, ky, col0, col1 - col0)) != hipSuccess) return e;
       if ((e = launch_lora_finalize(lg, t.spart, sp, true, col0, s)) != hipSuccess) return e;
       if ((e = skinny_rows(t.t2f, rows, X, kx, 0, round_up(in, 64))) != hipSuccess) return e;
