@@ -87,17 +87,22 @@ SkinnyPlan skinny_plan(int N, int K, int workgroups, int max_slots) {
   return p;
 }
 
-constexpr long long kStreamElems = 24 << 20;
+constexpr long long kStreamElems = 24 << 20, kStreamElemsFew = 14 << 20;
 hipError_t launch_skinny(const SkinnyArgs& a, const SkinnyPlan& p, hipStream_t st) {
   if (a.M <= 0 || a.N <= 0) return hipSuccess;
   if (a.M > 128 || !skinny_plan_ok(p, a.N, a.K) || (long long)frag_elems(a.N, a.K) * 2 >= (1ll << 31))
     return hipErrorInvalidValue;
-  // Past the caches where the model asks for it (its weights do not fit the last-level cache), from 48 MB a product on and up
-  // to 64 rows.  One product, us, one row, through the caches / past them: 180 MB 33.7 / 31.5, 104 MB 20.2 / 19.3, 52 MB
-  // 12.2 / 11.7, 46 MB 10.6 / 10.8, 34 MB 8.7 / 8.6, 19 MB 6.6 / 7.1, 12 MB 5.4 / 5.7.  All products of a decode with every one
-  // past the caches: d = 4096, eight layers, 1 / 64 / 128 rows 3800 -> 3612, 5219 -> 5055, 6878 -> 6861; but d = 2048, eight
-  // layers 1484 -> 1556, 2425 -> 2489, 3319 -> 3547; d = 1024, 16 layers 1775 -> 1889, 3175 -> 3403, 4979 -> 5205.
-  const bool stream = a.stream && a.M <= 64 && (long long)a.N * a.K >= kStreamElems;
+  // Past the caches where the model asks for it (its weights do not fit the last-level cache): up to 32 rows from 28 MB a
+  // product on, up to 64 rows from 48 MB on.  One product, us, one row, through the caches / past them: 180 MB 33.7 / 31.5,
+  // 104 MB 20.2 / 19.3, 52 MB 12.2 / 11.7, 46 MB 10.6 / 10.8, 34 MB 8.7 / 8.6, 19 MB 6.6 / 7.1, 12 MB 5.4 / 5.7.  What a
+  // product of 28 to 48 MB leaves in the caches displaces the smaller ones' weights, and counts up to 32 rows.  Whole rollout
+  // steps, us, every product past the caches / from 28 MB / from 48 MB: d = 2048, four layers, 1, 16, 24, 32 environments
+  // 1589 / 1527 / 1574, 2032 / 1977 / 2015, 2521 / 2468 / 2493, - / 2626 / 2637; d = 2816, four layers, 1, 16, 24
+  // 1803 / 1804 / 1830, 2549 / 2540 / 2580, 3077 / 3075 / 3124; but from 28 MB / from 48 MB with 64 environments
+  // d = 2048, eight layers 7654 / 7592, d = 2304, five layers 5201 / 5150, d = 2560, four layers 4357 / 4319.  Above 64 rows
+  // (all products of a decode, 128 rows, through the caches / every one past them): d = 4096, eight layers 6878 / 6861, d =
+  // 2048, eight layers 3319 / 3547.
+  const bool stream = a.stream && a.M <= 64 && (long long)a.N * a.K >= (a.M <= 32 ? kStreamElemsFew : kStreamElems);
   return stream ? launch_rows<false, true>(a, p, st) : launch_rows<false, false>(a, p, st);
 }
 

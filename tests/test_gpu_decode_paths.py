@@ -80,6 +80,33 @@ def test_decode_attention_variants_give_the_same_bits(head_dim):
     S.model.close()
 
 
+@pytest.mark.parametrize("d,ffn,layers", [(2048, 5504, 4), (2560, 8192, 2)])
+def test_weights_past_the_caches_give_the_same_bits(d, ffn, layers):
+    """Weights above 256 MB with products on both sides of 28 and 48 MB: environments decode to the bits that they get
+    among 65 (every product through the caches) at 1, 16 and 32 rows (past them from 28 MB on) and at 33 and 64 (from 48)."""
+    cfg = inputs.TINY.replace(name=f"past{d}", n_layers=layers, d_model=d, n_heads=d // 64, d_ffn=ffn, n_visual=16, batch=65,
+                              prompt_min=0, prompt_max=20)
+    fp = (ffn + 255) // 256 * 256
+    mb = sorted(2 * n / 2 ** 20 for n in (3 * d * d, d * d, 2 * fp * d, fp * d))
+    assert layers * sum(mb) > 256 and mb[0] < 28 and any(28 <= m < 48 for m in mb)
+    S = Setup(cfg, seed=17)
+    inp, dev = S.inputs(seed=17)
+    off = np.concatenate([[0], np.cumsum(inp.prompt_lens)])
+
+    def run(n):
+        S.model.prefill(dev["vis"][:n].contiguous(), dev["ids"][:off[n]].contiguous(), inp.prompt_lens[:n])
+        out = S.model.decode_actions(dev["gumbel"][:n].contiguous(), 1.5)
+        torch.cuda.synchronize()
+        return {k: v.clone() for k, v in out.items()}
+
+    full = run(65)
+    for n in (1, 16, 32, 33, 64):
+        got = run(n)
+        for k in full:
+            assert torch.equal(full[k][:n], got[k]), (k, n)
+    S.model.close()
+
+
 def test_persistent_decode_repeats_bit_exactly():
     S = Setup(inputs.L7B_B64.replace(n_layers=2), seed=12)
     S.model.debug_decode_path(1)
